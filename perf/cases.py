@@ -26,9 +26,9 @@ What each kind of call stands for:
 
 ASYNC is the mode in use.  The reproducible SYNC mode is taken for static
 runs on graphs without planted structure and for the state a dynamic case
-on them starts from, since ASYNC results there differ from run to run.  A
-static pass names every community by its first vertex, as a program does
-that compares one clustering with the next.
+on them starts from, since ASYNC results there differ from run to run.  An
+ASYNC static pass names every community by its first vertex of a fixed
+sample, as a program does that compares one clustering with the next.
 """
 from __future__ import annotations
 
@@ -288,7 +288,8 @@ def prepare(case, seed):
     cls = lib.StateF if real else lib.State
     if kind.startswith("static"):
         s["state"] = cls.empty(n)
-        s["ids"] = torch.arange(n, dtype=torch.int32, device=DEV)
+        s["ids"] = (torch.arange(0, n, max(1, n // 16_384), dtype=torch.int32, device=DEV)
+                    if case["mode"] == "async" else None)
         return s
     if case["graph"] == "rmat":
         s["state"] = lib.louvain_static(g, mode="sync")[0]
@@ -377,10 +378,12 @@ def _state(st):
 
 
 def _named(st, ids):
-    """Per vertex: the first vertex of its community, and the community's
-    total and size."""
+    """Per vertex: the first sampled vertex of its community, and the
+    community's total and size."""
+    if ids is None:
+        return _state(st)
     c = st.C.long()
-    first = torch.empty_like(ids).fill_(ids.numel()).scatter_reduce_(0, c, ids, "amin")
+    first = torch.full_like(st.C, st.C.numel()).scatter_reduce_(0, c[ids], ids, "amin")
     return {"C": first[c], "K": st.K, "Sigma": st.Sigma[c], "size": st.size[c]}
 
 
