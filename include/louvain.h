@@ -152,7 +152,8 @@ typedef struct {
   int32_t bin_launches[LV_NBINS];
   /* Launches bracketed by timing events (lv_set_timing) and their summed
    * GPU time, per timed kernel (index LV_TIME_*); zero for kernels that are
-   * not timed. */
+   * not timed.  A launch that bins the frontier, or prepares the hub rows,
+   * of several sub-rounds at once counts as one per sub-round. */
   int32_t timed_launches[LV_NTIMED];
   double timed_ms[LV_NTIMED];
 } lv_stats;

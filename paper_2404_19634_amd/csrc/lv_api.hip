@@ -51,7 +51,9 @@ lv_status fail(lv_status code, const char* msg) {
 // read back into plain host memory, and no HIP events are created or
 // recorded (no timing), so the call allocates nothing.
 thread_local bool g_no_alloc = false;
-thread_local int64_t g_plain_host[CTR_COUNT + kCtrLine];
+constexpr int kHostSlots = CTR_COUNT + kCtrLine;             // counter readback, then
+constexpr int kHostTotal = kHostSlots + (kPlanHost + 1) / 2;  // the plan's
+thread_local int64_t g_plain_host[kHostTotal];
 
 // Small pinned buffer for counter readback, one per host thread.
 struct Pinned {
@@ -69,7 +71,7 @@ lv_status pinned(int64_t** out) {
   }
   if (!g_pinned.p) {
     void* q = nullptr;
-    LV_HIP(hipHostMalloc(&q, sizeof(int64_t) * (CTR_COUNT + kCtrLine), hipHostMallocDefault));
+    LV_HIP(hipHostMalloc(&q, sizeof(int64_t) * kHostTotal, hipHostMallocDefault));
     g_pinned.p = static_cast<int64_t*>(q);
   }
   *out = g_pinned.p;
@@ -82,6 +84,7 @@ constexpr int kTimerPairs = 4096;
 struct Timer {
   std::vector<hipEvent_t> ev;   // 2 per launch, created on first use
   std::vector<int> kernel;      // kernel of each recorded pair
+  std::vector<int> weight;      // launches it counts as
   int used = 0;                 // pairs handed out since the last collect
   ~Timer() {
     for (hipEvent_t e : ev) (void)hipEventDestroy(e);
@@ -101,19 +104,28 @@ TimerPair timer_pair(int kernel) {
     if (hipEventCreate(&e) != hipSuccess) return p;
     t.ev.push_back(e);
   }
-  if (static_cast<int>(t.kernel.size()) < t.used + 1) t.kernel.resize(t.used + 1);
+  if (static_cast<int>(t.kernel.size()) < t.used + 1) {
+    t.kernel.resize(t.used + 1);
+    t.weight.resize(t.used + 1);
+  }
+  p.id = t.used;
+  t.weight[t.used] = 1;
   p.start = t.ev[2 * t.used];
   p.stop = t.ev[2 * t.used + 1];
   t.kernel[t.used++] = kernel;
   return p;
 }
 
+void timer_weight(const TimerPair& p, int launches) {
+  if (p.id >= 0) g_timer.weight[p.id] = launches;
+}
+
 void timer_collect(int32_t* launches, double* ms) {
   Timer& t = g_timer;
   for (int k = 0; k < t.used; ++k) {
     float x = 0.f;
-    if (hipEventElapsedTime(&x, t.ev[2 * k], t.ev[2 * k + 1]) == hipSuccess) {
-      launches[t.kernel[k]] += 1;
+    if (t.weight[k] && hipEventElapsedTime(&x, t.ev[2 * k], t.ev[2 * k + 1]) == hipSuccess) {
+      launches[t.kernel[k]] += t.weight[k];
       ms[t.kernel[k]] += x;
     }
   }
@@ -291,6 +303,7 @@ std::vector<SubRound> sub_rounds(int32_t mode, int32_t pass, int64_t est_frontie
     const int kk = pass > 0 ? (n <= kSmallLevel ? k : std::min(k, 4)) : k;
     for (int r = 0; r < (1 << kk); ++r) {
       SubRound s = all;
+      s.key = r;
       s.hash_round = static_cast<uint32_t>(r);
       s.hash_shift = 32u - static_cast<uint32_t>(kk);
       out.push_back(s);
@@ -299,6 +312,7 @@ std::vector<SubRound> sub_rounds(int32_t mode, int32_t pass, int64_t est_frontie
     const int64_t R = int64_t(1) << k;
     for (int64_t r = 0; r < R; ++r) {
       SubRound s = all;
+      s.key = static_cast<int32_t>(r);
       s.id_lo = static_cast<int32_t>(n * r / R);
       s.id_hi = static_cast<int32_t>(n * (r + 1) / R);
       out.push_back(s);
@@ -315,6 +329,7 @@ std::vector<SubRound> sub_rounds(int32_t mode, int32_t pass, int64_t est_frontie
       for (int v = 0; v < visits; ++v)
         for (int r = 0; r < (1 << kh); ++r) {
           SubRound s = all;
+          s.key = (c << kh) | r;
           s.deg_lo = cls_lo[c];
           s.deg_hi = cls_hi[c];
           if (kh > 0) {
@@ -329,6 +344,23 @@ std::vector<SubRound> sub_rounds(int32_t mode, int32_t pass, int64_t est_frontie
 }
 
 }  // namespace
+
+PlanKeys lv_plan_keys(const std::vector<SubRound>& plan, const lv_tuning& tu) {
+  PlanKeys k;
+  if (plan.size() <= 1) return k;
+  for (const SubRound& r : plan) k.rounds = std::max(k.rounds, r.key + 1);
+  if (plan[0].deg_lo > 0) {  // four degree classes, highest first
+    k.by_class = 1;
+    for (int c = 1; c < k.rounds / 4; c <<= 1) ++k.hash_bits;
+    k.twice = tu.revisit_min_degree <= 0 ? 0 : (tu.revisit_min_degree < 17 ? 3 : tu.revisit_min_degree < 129 ? 2
+                                                : tu.revisit_min_degree < 1025 ? 1 : 0);
+  } else if (plan[0].hash_shift == 32) {
+    k.by_id = 1;
+  } else {
+    k.hash_bits = 32 - static_cast<int>(plan[0].hash_shift);
+  }
+  return k;
+}
 
 std::vector<SubRound> lv_sub_rounds(int32_t mode, int32_t pass, int64_t est_frontier, int32_t n,
                                     const lv_tuning& tu) {
@@ -390,6 +422,65 @@ float ms_between(hipEvent_t a, hipEvent_t b) {
 float ms_between(hipEvent_t* ev, int a, int b) {
   if (!ev) return 0.f;
   return ms_between(ev[a], ev[b]);
+}
+
+// The sub-rounds of one iteration from a plan of the whole frontier.  With
+// more than one the host reads the counts back and launches what is there;
+// a single round's scans read them on the device.
+lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const std::vector<SubRound>& plan,
+                         int64_t* host, lv_stats& S, hipStream_t st) {
+  const PlanKeys pk = lv_plan_keys(plan, tu);
+  TimerPair tb = timer_pair(LV_TIME_BINNING), th;
+  if (plan.size() > 1) th = timer_pair(LV_TIME_HUB_CLEAR);  // (a single round's clear is its own launch)
+  launch_plan(a, ws, pk, &tb, &th, st);
+  ScanLists L{};
+  if (plan.size() == 1) {
+    for (int b = 0; b < NBINS; ++b) {
+      L.list[b] = ws.bins[b];
+      L.cnt[b] = -1;
+      S.bin_launches[b] += 1;
+    }
+    L.units = L.cunits = -1;
+    L.clear = true;
+    launch_scan(a, ws, tu, L, bins_for_degrees(0, 0x7fffffff, a.wave_max), st);
+    return LV_OK;
+  }
+  int32_t* h = reinterpret_cast<int32_t*>(host + kHostSlots);
+  LV_HIP(hipMemcpyAsync(h, plan_buf(ws).cnt, sizeof(int32_t) * kPlanHost, hipMemcpyDeviceToHost, st));
+  LV_HIP(hipStreamSynchronize(st));
+  int32_t first[kPlanKeys];  // list entries of all keys, in key order
+  int32_t run = 0;
+  for (int k = 0; k < pk.rounds * 8; ++k) {
+    first[k] = run;
+    if (k % 8 < NBINS) run += h[k];
+  }
+  const int32_t *ub = h + kPlanKeys, *un = ub + kPlanRounds, *cb = un + kPlanRounds, *cn = cb + kPlanRounds,
+                *hf = cn + kPlanRounds, *tail = hf + kPlanRounds;
+  L.clear = tail[PT_MAXDEG] > kHubPartMaxDeg;
+  int served = 0, hub_rounds = 0;
+  for (const SubRound& r : plan) {
+    uint32_t mask = 0;
+    for (int b = 0; b < NBINS; ++b) {
+      L.cnt[b] = h[r.key * 8 + b];
+      L.list[b] = ws.bins[0] + first[r.key * 8 + b];
+      if (!L.cnt[b]) continue;
+      mask |= 1u << b;
+      S.bin_launches[b] += 1;
+    }
+    if (!mask) continue;
+    const bool hubs = mask & (1u << BIN_HUB);
+    ++served;
+    hub_rounds += hubs ? 1 : 0;
+    L.units = hubs ? un[r.key] : 0;
+    L.cunits = hubs ? cn[r.key] : 0;
+    L.ubase = hubs ? ub[r.key] : 0;
+    L.cbase = hubs ? cb[r.key] : 0;
+    L.hub_first = hubs ? hf[r.key] : 0;
+    launch_scan(a, ws, tu, L, mask, st);
+  }
+  timer_weight(tb, std::max(1, served));
+  timer_weight(th, L.clear ? 0 : hub_rounds);
+  return LV_OK;
 }
 
 // resume_li > 0: the local-moving iterations of pass 0 already ran (the
@@ -557,7 +648,20 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       // degree classes); grids are sized for that
       a.est = std::max<int64_t>(64, est_frontier * 4 / static_cast<int64_t>(plan.size()));
       a.sparse = (est_frontier * 8 <= L.n || (pass > 0 && L.n <= kSmallLevel)) ? 1 : 0;
-      for (size_t r = 0; r < plan.size(); ++r, ++round_seq) {
+      // The frontier is sorted once for all sub-rounds (plan.hip) when it is
+      // dense, or when there are many sub-rounds; a sparse frontier in a few
+      // rounds is cheaper to pick from its list, with no readback in between
+      // (a 16,000-update batch's two rounds: 10 us each, the readback 15).
+      const bool planned = !a.sparse || pass > 0 || plan.size() >= 8;
+      if (planned) {
+        a.rc = ws.ctr + CTR_ROUND0 + (round_seq & 1) * kRoundSet;
+        a.rc_next = ws.ctr + CTR_ROUND0 + ((round_seq + 1) & 1) * kRoundSet;
+        a.sc = sc;
+        a.sc_next = sc_next;
+        ++round_seq;
+        if ((s = planned_rounds(a, ws, tu, plan, host, S, st))) return s;
+      }
+      for (size_t r = 0; r < plan.size() && !planned; ++r, ++round_seq) {
         a.rc = ws.ctr + CTR_ROUND0 + (round_seq & 1) * kRoundSet;
         a.rc_next = ws.ctr + CTR_ROUND0 + ((round_seq + 1) & 1) * kRoundSet;
         a.sc = sc;

@@ -361,6 +361,41 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h) {
   return h;
 }
 
+// Degree bins and the units of hub rows (binning and the scan share them).
+__device__ __forceinline__ int bin_of(int32_t deg, int32_t wave_max) {
+  if (deg <= 0) return -1;
+  if (deg <= 4) return BIN_G4;
+  if (deg <= 8) return BIN_G8;
+  if (deg <= 16) return BIN_G16;
+  if (deg <= 32) return BIN_G32;
+  if (deg <= wave_max) return BIN_WAVE;
+  if (deg <= kBlockMaxDegree) return BIN_BLOCK;
+  return BIN_HUB;
+}
+
+// rows above this keep a global table; shorter hub rows aggregate by segment
+constexpr int32_t kHubPartMaxDeg = 1 << 20;
+__device__ __forceinline__ int64_t hub_units(int32_t deg) { return (deg + kHubUnitArcs - 1) / kHubUnitArcs; }
+__device__ __forceinline__ int64_t hub_cunits(int32_t deg) {
+  return (2 * static_cast<int64_t>(deg) + kHubClearSlots - 1) / kHubClearSlots;
+}
+
+__device__ __forceinline__ bool hub_part(int32_t deg) { return deg <= kHubPartMaxDeg; }
+__device__ __forceinline__ int64_t hub_slots(int32_t deg) {
+  const int64_t base = 2 * static_cast<int64_t>(deg);
+  return hub_part(deg) ? base + (hub_units(deg) * (hub_cunits(deg) + 1) + 1) / 2 : base;
+}
+
+struct HubOut {
+  int64_t* off;    // global table offset
+  int64_t* cbase;  // first clear / decide unit
+  int32_t* cnum;   // number of clear / decide units
+  int32_t* u_b;    // insert units: (hub item, first arc)
+  int64_t* u_a;
+  int32_t* c_b;    // clear / decide units: (hub item, first slot)
+  int64_t* c_s;
+};
+
 // --------------------------------------------------------------------------
 // Launchers (host).  All enqueue on `st`; none synchronises.
 // --------------------------------------------------------------------------
@@ -531,6 +566,7 @@ struct MoveArgs {
 // One ASYNC sub-round: vertices whose id hash matches (hash_shift = 32: all),
 // ids in [id_lo, id_hi), row lengths in [deg_lo, deg_hi].
 struct SubRound {
+  int32_t key = 0;  // its index in the iteration's plan
   uint32_t hash_round = 0;
   uint32_t hash_shift = 32;
   int32_t id_lo = 0;
@@ -538,6 +574,47 @@ struct SubRound {
   int32_t deg_lo = 0;
   int32_t deg_hi = 0x7fffffff;
 };
+// The iteration's plan (plan.hip): the frontier sorted by (sub-round, bin).
+// Keys of a vertex: its degree class (by_class: > 1024, 129.., 17.., the
+// rest; the first `twice` classes are visited twice), the top hash_bits of
+// its id hash, or its id range (by_id).
+constexpr int kPlanRounds = 128;
+constexpr int kPlanKeys = kPlanRounds * 8;
+struct PlanKeys {
+  int32_t rounds = 1;
+  int32_t hash_bits = 0;
+  int32_t by_class = 0;
+  int32_t by_id = 0;
+  int32_t twice = 0;
+};
+enum PlanTail { PT_MAXDEG = 0, PT_UNITS, PT_CUNITS, kPlanTail = 16 };
+struct PlanBuf {
+  int32_t* cnt;     // per key (8 per sub-round); with the five arrays below read back by the host
+  int32_t* hub_ubase;   // per sub-round: first insert unit, their number,
+  int32_t* hub_units;
+  int32_t* hub_cbase;   // first clear / decide unit, their number,
+  int32_t* hub_cunits;
+  int32_t* hub_first;   // and first hub item
+  int32_t* tail;        // PlanTail
+  int32_t* cursor;  // per key: next list entry
+  int64_t* arcs;    // per key
+};
+constexpr int kPlanHost = kPlanKeys + 5 * kPlanRounds + kPlanTail;  // int32 entries read back
+PlanBuf plan_buf(const Workspace& ws);
+struct TimerPair;
+void launch_plan(const MoveArgs& a, Workspace& ws, const PlanKeys& pk, TimerPair* binning, TimerPair* hubs,
+                 hipStream_t st);
+// The scans of one sub-round whose lists a plan has made.
+struct ScanLists {
+  int32_t* list[NBINS];
+  int32_t cnt[NBINS];      // items per bin (-1: in the sub-round counters)
+  int32_t units, cunits;   // hub units (-1: likewise)
+  int64_t hub_first, ubase, cbase;  // where the sub-round's hub items and units start
+  bool clear;              // a hub row has a global table to clear
+};
+void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const ScanLists& s, uint32_t bin_mask,
+                 hipStream_t st);
+
 // Measurement hook (lv_set_timing): the start and stop events of one launch
 // of a timed kernel, for hipExtLaunchKernelGGL, which stamps them with the
 // kernel's own begin and end times from its dispatch (both null when the
@@ -545,7 +622,10 @@ struct SubRound {
 struct TimerPair {
   hipEvent_t start = nullptr;
   hipEvent_t stop = nullptr;
+  int id = -1;
 };
+// The launch of a pair served `launches` sub-rounds (0: it is not reported).
+void timer_weight(const TimerPair& p, int launches);
 TimerPair timer_pair(int kernel);
 void timer_collect(int32_t* launches, double* ms);  // adds per kernel, resets
 

@@ -67,6 +67,10 @@ struct Dev {
   const int64_t* two_m;
   int32_t mode;
   int32_t guard;
+  // items per bin and hub units of the round, where the host knows them
+  // (-1: in the sub-round counters)
+  int32_t cnt[NBINS];
+  int32_t units, cunits;
   int32_t defer;  // ASYNC: Sigma / size changes through the workgroup aggregate
   HotRec* hot;    // ASYNC with defer: record buffer of large communities' changes (else null)
 };
@@ -95,6 +99,14 @@ Dev make_dev(const MoveArgs& a, Workspace& ws, const lv_tuning& tu) {
   d.defer = tu.defer_totals;
   d.hot = (a.mode == LV_ASYNC && tu.defer_totals) ? ws.hot : nullptr;
   return d;
+}
+
+__device__ __forceinline__ int64_t bin_count(const Dev& D, int b) {
+  return D.cnt[b] >= 0 ? D.cnt[b] : D.rc[rc_bin(b)];
+}
+__device__ __forceinline__ int64_t unit_count(const Dev& D) { return D.units >= 0 ? D.units : D.rc[RC_HUB_UNITS]; }
+__device__ __forceinline__ int64_t cunit_count(const Dev& D) {
+  return D.cunits >= 0 ? D.cunits : D.rc[RC_HUB_CUNITS];
 }
 
 // 2m of the call; 0 when it is out of range (the first kernel of the call
@@ -286,7 +298,7 @@ __device__ __forceinline__ void agg_end_moves(A* a, const Dev& D, int64_t two_m)
 // with one atomic, so a community gets at most kHotRegions atomics.
 constexpr int64_t kHotMinFrontier = 1 << 16;  // frontier estimate of a launch that defers
 constexpr int kHotSlots = 2048;
-__global__ void __launch_bounds__(kBlock) k_hot_apply(const int64_t* __restrict__ rc, const HotRec* __restrict__ hot,
+__global__ void __launch_bounds__(kBlock) k_hot_apply(int64_t* __restrict__ rc, const HotRec* __restrict__ hot,
                                                      int64_t* __restrict__ Sigma, int32_t* __restrict__ size) {
   __shared__ int32_t key[kHotSlots];
   __shared__ unsigned long long dk[kHotSlots];
@@ -329,6 +341,8 @@ __global__ void __launch_bounds__(kBlock) k_hot_apply(const int64_t* __restrict_
     }
   }
   __syncthreads();
+  // (the next sub-round of a plan uses the same counters)
+  if (threadIdx.x == 0) rc[RC_HOT + blockIdx.x * kCtrLine] = 0;
   for (int t = threadIdx.x; t < kHotSlots; t += kBlock) {
     const int32_t c = key[t];
     if (c < 0) continue;
@@ -378,32 +392,6 @@ struct Bins {
   int32_t* list[NBINS];
 };
 
-__device__ __forceinline__ int bin_of(int32_t deg, int32_t wave_max) {
-  if (deg <= 0) return -1;
-  if (deg <= 4) return BIN_G4;
-  if (deg <= 8) return BIN_G8;
-  if (deg <= 16) return BIN_G16;
-  if (deg <= 32) return BIN_G32;
-  if (deg <= wave_max) return BIN_WAVE;
-  if (deg <= kBlockMaxDegree) return BIN_BLOCK;
-  return BIN_HUB;
-}
-
-struct HubOut {
-  int64_t* off;    // global table offset
-  int64_t* cbase;  // first clear / decide unit
-  int32_t* cnum;   // number of clear / decide units
-  int32_t* u_b;    // insert units: (hub item, first arc)
-  int64_t* u_a;
-  int32_t* c_b;    // clear / decide units: (hub item, first slot)
-  int64_t* c_s;
-};
-
-__device__ __forceinline__ int64_t hub_units(int32_t deg) { return (deg + kHubUnitArcs - 1) / kHubUnitArcs; }
-__device__ __forceinline__ int64_t hub_cunits(int32_t deg) {
-  return (2 * static_cast<int64_t>(deg) + kHubClearSlots - 1) / kHubClearSlots;
-}
-
 // Hub rows up to kHubPartMaxDeg arcs aggregate by segment: each insert unit
 // sums its arcs per community in LDS and writes the (community, weight)
 // pairs grouped by segment (a hash range of community ids, one per decide
@@ -412,18 +400,11 @@ __device__ __forceinline__ int64_t hub_cunits(int32_t deg) {
 // Longer rows use the global table.  A partitioned row's pool reservation
 // holds its pairs (unit u at slot u * kHubUnitArcs) and, after 2 * deg
 // slots, the segment offsets of every unit (hub_cunits + 1 int32 each).
-constexpr int32_t kHubPartMaxDeg = 1 << 20;
 constexpr int kHubMaxSegs = (2 * kHubPartMaxDeg + kHubClearSlots - 1) / kHubClearSlots;
 constexpr int kHubMaxUnits = (kHubPartMaxDeg + kHubUnitArcs - 1) / kHubUnitArcs;
 
 static_assert(kHubMaxSegs + 1 <= 4 * kBlock && kHubMaxUnits + 1 <= 4 * kBlock,
               "segment offsets and unit counts must fit one workgroup scan");
-
-__device__ __forceinline__ bool hub_part(int32_t deg) { return deg <= kHubPartMaxDeg; }
-__device__ __forceinline__ int64_t hub_slots(int32_t deg) {
-  const int64_t base = 2 * static_cast<int64_t>(deg);
-  return hub_part(deg) ? base + (hub_units(deg) * (hub_cunits(deg) + 1) + 1) / 2 : base;
-}
 
 // A hub row's table offset and first clear / decide unit.
 __device__ __forceinline__ void hub_head(const HubOut& H, int64_t pos, int32_t deg, int64_t off, int64_t bc) {
@@ -815,7 +796,7 @@ template <int G>
 __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const int32_t* __restrict__ list, int bin,
                                            int64_t rb, int64_t nb, MoveAgg* agg) {
   constexpr int VPW = kWave / G;
-  const int64_t count = D.rc[rc_bin(bin)];
+  const int64_t count = bin_count(D, bin);
   const int lane = lane_id();
   const int sub = lane / G;
   const int k = lane % G;
@@ -906,7 +887,7 @@ __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const in
 // communities is summed in registers, with no exchange between lanes.
 __device__ __forceinline__ void role_lane4(const Dev& D, int64_t two_m, const int32_t* __restrict__ list, int64_t rb,
                                            int64_t nb, MoveAgg* agg) {
-  const int64_t count = D.rc[rc_bin(BIN_G4)];
+  const int64_t count = bin_count(D, BIN_G4);
   const int64_t nt = nb * blockDim.x;
   int64_t gain_acc = 0, moved = 0, marcs = 0;
   for (int64_t idx = rb * blockDim.x + threadIdx.x; idx < count; idx += nt) {
@@ -974,7 +955,7 @@ constexpr int kDecideSlots = 4;
 template <int TS>
 __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int32_t* __restrict__ list, int64_t rb,
                                           int64_t nb, int32_t* s_keys, int32_t* s_vals, MoveAgg* agg) {
-  const int64_t count = D.rc[rc_bin(BIN_WAVE)];
+  const int64_t count = bin_count(D, BIN_WAVE);
   const int lane = lane_id();
   const int wid = threadIdx.x / kWave;
   int32_t* keys = s_keys + wid * TS;
@@ -1185,7 +1166,7 @@ struct Red {
 // Rows up to kBlockMaxDegree: one workgroup, LDS table of up to 4096 slots.
 __device__ __forceinline__ void role_block(const Dev& D, int64_t two_m, const int32_t* __restrict__ list, int64_t rb,
                                            int64_t nb, int32_t* keys, int32_t* vals, Red* red) {
-  const int64_t count = D.rc[rc_bin(BIN_BLOCK)];
+  const int64_t count = bin_count(D, BIN_BLOCK);
   int64_t gain_acc = 0, moved = 0, marcs = 0;
   // the next row's id and metadata are loaded while this row is scanned
   // (no other workgroup changes C of a row this workgroup holds)
@@ -1329,7 +1310,7 @@ struct HubIn {
 
 __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, int64_t rb, int64_t nb, int32_t* tk,
                                                 int32_t* tv, int32_t* hist, Red* red) {
-  const int64_t count = D.rc[RC_HUB_UNITS];
+  const int64_t count = unit_count(D);
   for (int64_t u = rb; u < count; u += nb) {
     const int32_t h = H.u_b[u];
     const int32_t i = H.list[h];
@@ -1530,7 +1511,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_clear(Dev D, const int32_t* __re
                                                      const int32_t* __restrict__ c_b, const int64_t* __restrict__ c_s,
                                                      unsigned long long* __restrict__ tab,
                                                      int64_t* __restrict__ hub_kid, int64_t pool_slots) {
-  const int64_t count = D.rc[RC_HUB_CUNITS];
+  const int64_t count = cunit_count(D);
   for (int64_t u = blockIdx.x; u < count; u += gridDim.x) {
     const int32_t h = c_b[u];
     const int32_t deg = D.row_len[list[h]];
@@ -1593,7 +1574,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_decide(Dev D, const int32_t* __r
   __shared__ int32_t s_w[kBlock / kWave];
   const int64_t two_m = load_two_m(D);
   if (two_m == 0) return;
-  const int64_t count = D.rc[RC_HUB_CUNITS];
+  const int64_t count = cunit_count(D);
   for (int64_t u = blockIdx.x; u < count; u += gridDim.x) {
     const int32_t h = c_b[u];
     const int32_t i = list[h];
@@ -1710,9 +1691,10 @@ __global__ void __launch_bounds__(kBlock) k_hub_final(Dev D, const int32_t* __re
                                                      const int32_t* __restrict__ hub_cnum,
                                                      const int64_t* __restrict__ unit_g,
                                                      const int32_t* __restrict__ unit_c,
-                                                     int32_t* __restrict__ hub_moved) {
+                                                     int32_t* __restrict__ hub_moved,
+                                                     int64_t* __restrict__ hub_kid) {
   if (load_two_m(D) == 0) return;
-  const int64_t count = D.rc[rc_bin(BIN_HUB)];
+  const int64_t count = bin_count(D, BIN_HUB);
   const int lane = lane_id();
   const int64_t wave = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) / kWave;
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
@@ -1740,6 +1722,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_final(Dev D, const int32_t* __re
       const int32_t d = D.C[i];
       const bool mv = decide_move(D, d, bc, bg);
       hub_moved[h] = mv ? 1 : 0;
+      hub_kid[h] = 0;  // (a planned sub-round may be visited again)
       if (mv) {
         commit_move(D, static_cast<MoveAggSmall*>(nullptr), i, d, bc, D.K[i]);
         gain_acc += bg;
@@ -1756,7 +1739,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_final(Dev D, const int32_t* __re
 __global__ void __launch_bounds__(kBlock) k_hub_expand(Dev D, const int32_t* __restrict__ list,
                                                       const int32_t* __restrict__ u_b, const int64_t* __restrict__ u_a,
                                                       const int32_t* __restrict__ hub_moved) {
-  const int64_t count = D.rc[RC_HUB_UNITS];
+  const int64_t count = unit_count(D);
   for (int64_t u = blockIdx.x; u < count; u += gridDim.x) {
     const int32_t h = u_b[u];
     if (!hub_moved[h]) continue;
@@ -2066,10 +2049,9 @@ uint32_t bins_for_degrees(int32_t lo, int32_t hi, int32_t wave_max) {
   return m;
 }
 
-void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
-                  hipStream_t st) {
+void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const ScanLists& S, uint32_t bin_mask,
+                 hipStream_t st) {
   Dev D = make_dev(a, ws, tu);
-  const int64_t words = (static_cast<int64_t>(a.g.n) + 31) / 32;
   // Large communities' changes are deferred only in a fused launch over a
   // frontier large enough for their atomics to queue (a smaller one does not
   // repay the extra launch); the launches per bin of a dense frontier run in
@@ -2077,41 +2059,47 @@ void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const S
   const bool fuse = a.sparse && a.est <= tu.fuse_max_frontier;
   if (!fuse || a.est < kHotMinFrontier) D.hot = nullptr;
   Bins b;
-  for (int k = 0; k < NBINS; ++k) b.list[k] = ws.bins[k];
-  HubOut HO{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
-  const TimerPair tb = timer_pair(LV_TIME_BINNING);
-  // (a listed frontier has at most a.est vertices; a bitmask walk is a
-  // grid-stride loop, so a smaller grid only slows it)
-  const int64_t bin_items = std::max<int64_t>(1, std::min<int64_t>(words, a.est));
-  hipExtLaunchKernelGGL(k_bin_frontier, dim3(grid_for(bin_items, kBlock * kBinPer, 4096)), dim3(kBlock), 0, st, tb.start,
-                        tb.stop, 0, const_cast<uint32_t*>(a.cur), a.cur_fl, a.sc_next ? a.next_fl.cnt : nullptr,
-                        a.range, a.ever, a.g.row_len, a.g.n, a.wave_max,
-                        r.hash_round, r.hash_shift, r.id_lo, r.id_hi, r.deg_lo, r.deg_hi, a.clear_cur, b, HO, a.rc,
-                        a.sc, a.rc_next, a.sc_next);
-
+  for (int k = 0; k < NBINS; ++k) {
+    b.list[k] = S.list[k];
+    D.cnt[k] = S.cnt[k];
+  }
+  D.units = S.units;
+  D.cunits = S.cunits;
+  // grids: the items when known, else the bound on the frontier
   const int64_t est = a.est > 0 ? a.est : 1;
-  const int bs = grid_by_est(est, 64, tu.blocks_small);  // sub-wavefront groups
-  const int b4 = grid_by_est(est, 256, tu.blocks_small);  // one row per lane
-  const int bw = grid_by_est(est, 4, tu.blocks_wave);    // one row per wavefront
-  const int bh = grid_by_est(est, 1, tu.blocks_hub);     // one row / unit per workgroup
+  auto grid = [&](int bin, int64_t rows_per_block, int max_blocks) {
+    return S.cnt[bin] >= 0 ? grid_by_est(S.cnt[bin], rows_per_block, max_blocks)
+                           : grid_by_est(est, bin <= BIN_G32 ? (bin == BIN_G4 ? 256 : 64) : rows_per_block, max_blocks);
+  };
+  const int bh = grid_by_est(est, 1, tu.blocks_hub);  // one row / unit per workgroup
+  const int bu = S.units >= 0 ? grid_by_est(S.units, 1, tu.blocks_hub) : bh;
+  const int bc = S.cunits >= 0 ? grid_by_est(S.cunits, 1, tu.blocks_hub) : bh;
+  const int per[NBINS] = {grid(BIN_G4, 256, tu.blocks_small), grid(BIN_G8, 32, tu.blocks_small),
+                          grid(BIN_G16, 16, tu.blocks_small), grid(BIN_G32, 8, tu.blocks_small),
+                          grid(BIN_WAVE, 4, tu.blocks_wave), grid(BIN_BLOCK, 1, tu.blocks_hub), bu};
   const bool hubs = bin_mask & (1u << BIN_HUB);
-  if (hubs) {
+  const int32_t* hlist = S.list[BIN_HUB];
+  int64_t* h_off = ws.hub_off + S.hub_first;
+  int64_t* h_kid = ws.hub_kid + S.hub_first;
+  const int32_t* u_b = ws.u_ins_b + S.ubase;
+  const int64_t* u_a = ws.u_ins_a + S.ubase;
+  const int32_t* c_b = ws.u_emit_b + S.cbase;
+  const int64_t* c_s = ws.u_emit_s + S.cbase;
+  if (hubs && S.clear) {
     const TimerPair tc = timer_pair(LV_TIME_HUB_CLEAR);
-    hipExtLaunchKernelGGL(k_hub_clear, dim3(cap_grid(k_hub_clear, bh)), dim3(kBlock), 0, st, tc.start, tc.stop, 0, D,
-                          ws.bins[BIN_HUB], ws.hub_off, ws.u_emit_b, ws.u_emit_s,
-                          reinterpret_cast<unsigned long long*>(ws.pool_pairs), ws.hub_kid, ws.pool_slots);
+    hipExtLaunchKernelGGL(k_hub_clear, dim3(cap_grid(k_hub_clear, bc)), dim3(kBlock), 0, st, tc.start, tc.stop, 0, D,
+                          hlist, h_off, c_b, c_s, reinterpret_cast<unsigned long long*>(ws.pool_pairs), h_kid,
+                          ws.pool_slots);
   }
 
   // The scan: for a small, sparse frontier one launch whose role ranges lie
   // end to end; otherwise a launch per bin in increasing degree order, so
   // that (in ASYNC mode) each bin sees the moves of the bins before it (on
   // dense frontiers that ordering is worth modularity).
-  const int per[NBINS] = {b4, bs, bs, bs, bw, bh, bh};
   const int ts = table_slots_for(a.wave_max);
   const size_t lw = ts <= 128 ? lds_wave<128>() : ts <= 256 ? lds_wave<256>() : ts <= 512 ? lds_wave<512>()
                                                                                         : lds_wave<1024>();
-  const HubIn H{ws.bins[BIN_HUB], ws.hub_off, ws.u_ins_b, ws.u_ins_a,
-                reinterpret_cast<unsigned long long*>(ws.pool_pairs), ws.hub_kid, ws.pool_slots};
+  const HubIn H{hlist, h_off, u_b, u_a, reinterpret_cast<unsigned long long*>(ws.pool_pairs), h_kid, ws.pool_slots};
   if (fuse) {
     Roles R;
     int64_t end = 0;
@@ -2150,16 +2138,40 @@ void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const S
     hipLaunchKernelGGL(k_hot_apply, dim3(kHotRegions), dim3(kBlock), 0, st, a.rc, D.hot, a.Sigma, a.size);
   if (hubs) {
     const TimerPair td = timer_pair(LV_TIME_HUB_DECIDE);
-    hipExtLaunchKernelGGL(k_hub_decide, dim3(cap_grid(k_hub_decide, bh)), dim3(kBlock), 0, st, td.start, td.stop, 0,
-                          D, ws.bins[BIN_HUB], ws.hub_off, ws.u_emit_b, ws.u_emit_s,
-                          reinterpret_cast<const unsigned long long*>(ws.pool_pairs), ws.hub_kid, ws.unit_g,
-                          ws.unit_c, ws.pool_slots);
-    hipLaunchKernelGGL(k_hub_final, dim3(64), dim3(kBlock), 0, st, D, ws.bins[BIN_HUB], ws.hub_cbase, ws.hub_cnum,
-                       ws.unit_g, ws.unit_c, ws.hub_moved);
+    hipExtLaunchKernelGGL(k_hub_decide, dim3(cap_grid(k_hub_decide, bc)), dim3(kBlock), 0, st, td.start, td.stop, 0,
+                          D, hlist, h_off, c_b, c_s, reinterpret_cast<const unsigned long long*>(ws.pool_pairs), h_kid,
+                          ws.unit_g, ws.unit_c, ws.pool_slots);
+    const int bf = S.cnt[BIN_HUB] >= 0 ? grid_by_est(S.cnt[BIN_HUB], 4, 64) : 64;
+    hipLaunchKernelGGL(k_hub_final, dim3(bf), dim3(kBlock), 0, st, D, hlist, ws.hub_cbase + S.hub_first,
+                       ws.hub_cnum + S.hub_first, ws.unit_g, ws.unit_c, ws.hub_moved + S.hub_first, h_kid);
     if (a.push)
-      hipLaunchKernelGGL(k_hub_expand, dim3(cap_grid(k_hub_expand, bh)), dim3(kBlock), 0, st, D, ws.bins[BIN_HUB],
-                         ws.u_ins_b, ws.u_ins_a, ws.hub_moved);
+      hipLaunchKernelGGL(k_hub_expand, dim3(cap_grid(k_hub_expand, bu)), dim3(kBlock), 0, st, D, hlist, u_b, u_a,
+                         ws.hub_moved + S.hub_first);
   }
+}
+
+void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
+                  hipStream_t st) {
+  const int64_t words = (static_cast<int64_t>(a.g.n) + 31) / 32;
+  Bins b;
+  ScanLists S{};
+  for (int k = 0; k < NBINS; ++k) {
+    b.list[k] = S.list[k] = ws.bins[k];
+    S.cnt[k] = -1;
+  }
+  S.units = S.cunits = -1;
+  S.clear = true;
+  HubOut HO{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
+  const TimerPair tb = timer_pair(LV_TIME_BINNING);
+  // (a listed frontier has at most a.est vertices; a bitmask walk is a
+  // grid-stride loop, so a smaller grid only slows it)
+  const int64_t bin_items = std::max<int64_t>(1, std::min<int64_t>(words, a.est));
+  hipExtLaunchKernelGGL(k_bin_frontier, dim3(grid_for(bin_items, kBlock * kBinPer, 4096)), dim3(kBlock), 0, st, tb.start,
+                        tb.stop, 0, const_cast<uint32_t*>(a.cur), a.cur_fl, a.sc_next ? a.next_fl.cnt : nullptr,
+                        a.range, a.ever, a.g.row_len, a.g.n, a.wave_max,
+                        r.hash_round, r.hash_shift, r.id_lo, r.id_hi, r.deg_lo, r.deg_hi, a.clear_cur, b, HO, a.rc,
+                        a.sc, a.rc_next, a.sc_next);
+  launch_scan(a, ws, tu, S, bin_mask, st);
 }
 
 void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st) {
