@@ -432,7 +432,26 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
   const PlanKeys pk = lv_plan_keys(plan, tu);
   TimerPair tb = timer_pair(LV_TIME_BINNING), th;
   if (plan.size() > 1) th = timer_pair(LV_TIME_HUB_CLEAR);  // (a single round's clear is its own launch)
-  launch_plan(a, ws, pk, &tb, &th, st);
+  PlanArgs pa{};
+  pa.cur = const_cast<uint32_t*>(a.cur);
+  pa.range = a.range;
+  pa.ever = a.ever;
+  pa.row_len = a.g.row_len;
+  pa.n = a.g.n;
+  pa.wave_max = a.wave_max;
+  for (int b = 0; b < NBINS; ++b) pa.list[b] = ws.bins[b];
+  // the record buffer of the deferred totals: read back by the host, and by
+  // the plan's kernels, before the first scan of the iteration writes records
+  static_assert(sizeof(HotRec) * kHotRegions * kHotCap >= kPlanBytes, "plan counters fit the record buffer");
+  pa.mem = ws.hot;
+  pa.rc = a.rc;
+  pa.rc_next = a.rc_next;
+  pa.sc = a.sc;
+  pa.sc_next = a.sc_next;
+  pa.next_cnt = a.next_fl.cnt;
+  pa.hub = HubOut{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
+  pa.hub_kid = ws.hub_kid;
+  launch_plan(pa, pk, &tb, &th, st);
   ScanLists L{};
   if (plan.size() == 1) {
     for (int b = 0; b < NBINS; ++b) {
@@ -446,7 +465,7 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
     return LV_OK;
   }
   int32_t* h = reinterpret_cast<int32_t*>(host + kHostSlots);
-  LV_HIP(hipMemcpyAsync(h, plan_buf(ws).cnt, sizeof(int32_t) * kPlanHost, hipMemcpyDeviceToHost, st));
+  LV_HIP(hipMemcpyAsync(h, ws.hot, sizeof(int32_t) * kPlanHost, hipMemcpyDeviceToHost, st));
   LV_HIP(hipStreamSynchronize(st));
   int32_t first[kPlanKeys];  // list entries of all keys, in key order
   int32_t run = 0;

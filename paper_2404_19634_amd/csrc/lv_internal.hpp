@@ -587,7 +587,7 @@ struct PlanKeys {
   int32_t by_id = 0;
   int32_t twice = 0;
 };
-enum PlanTail { PT_MAXDEG = 0, PT_UNITS, PT_CUNITS, kPlanTail = 16 };
+enum PlanTail { PT_MAXDEG = 0, PT_UNITS, PT_CUNITS, PT_AFFECTED, kPlanTail = 16 };
 struct PlanBuf {
   int32_t* cnt;     // per key (8 per sub-round); with the five arrays below read back by the host
   int32_t* hub_ubase;   // per sub-round: first insert unit, their number,
@@ -596,14 +596,31 @@ struct PlanBuf {
   int32_t* hub_cunits;
   int32_t* hub_first;   // and first hub item
   int32_t* tail;        // PlanTail
-  int32_t* cursor;  // per key: next list entry
   int64_t* arcs;    // per key
+  int32_t* cursor;  // per key: next list entry
 };
 constexpr int kPlanHost = kPlanKeys + 5 * kPlanRounds + kPlanTail;  // int32 entries read back
-PlanBuf plan_buf(const Workspace& ws);
+constexpr size_t kPlanArcs = 4 * kPlanHost;                         // byte offset of arcs
+constexpr size_t kPlanBytes = kPlanArcs + 8 * kPlanKeys + 4 * kPlanKeys;
+static_assert(kPlanArcs % 8 == 0, "plan layout");
+PlanBuf plan_buf(void* mem);  // kPlanBytes of device memory
+struct PlanArgs {
+  uint32_t* cur;          // frontier; left clear
+  const uint32_t* range;  // null: every vertex in range
+  uint32_t* ever;         // null: not tracked
+  const int32_t* row_len;
+  int32_t n;
+  int32_t wave_max;
+  int32_t* list[NBINS];   // one sub-round: per bin; else list[0] for all
+  void* mem;
+  // counters of the integer path (null in the other: the host takes arcs
+  // and PT_AFFECTED from the plan)
+  int64_t *rc, *rc_next, *sc, *sc_next, *next_cnt;
+  HubOut hub;
+  int64_t* hub_kid;  // null: no hub units
+};
 struct TimerPair;
-void launch_plan(const MoveArgs& a, Workspace& ws, const PlanKeys& pk, TimerPair* binning, TimerPair* hubs,
-                 hipStream_t st);
+void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* binning, TimerPair* hubs, hipStream_t st);
 // The scans of one sub-round whose lists a plan has made.
 struct ScanLists {
   int32_t* list[NBINS];
@@ -641,6 +658,7 @@ void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st);
 // ASYNC iteration.
 lv_status lv_fail(lv_status code, const char* msg);
 lv_tuning lv_effective_tuning();
+PlanKeys lv_plan_keys(const std::vector<SubRound>& plan, const lv_tuning& tu);
 std::vector<SubRound> lv_sub_rounds(int32_t mode, int32_t pass, int64_t est_frontier, int32_t n,
                                     const lv_tuning& tu);
 

@@ -102,7 +102,8 @@ __global__ void k_plan_begin(PlanBuf p, int64_t* __restrict__ rc_next, int64_t* 
     p.arcs[k] = 0;
   }
   for (int k = threadIdx.x; k < kPlanTail; k += blockDim.x) p.tail[k] = 0;
-  for (int k = threadIdx.x; k < kRoundSet; k += blockDim.x) rc_next[k] = 0;
+  if (rc_next)
+    for (int k = threadIdx.x; k < kRoundSet; k += blockDim.x) rc_next[k] = 0;
   if (sc_next)
     for (int k = threadIdx.x; k < kStatSet; k += blockDim.x) sc_next[k] = 0;
   if (next_cnt)
@@ -181,6 +182,7 @@ __global__ void __launch_bounds__(kBlock) k_plan_scan(PlanKeys pk, PlanBuf p, in
     if (k < keys) p.cursor[k] = pk.rounds == 1 ? 0 : run;
     run += c[q];
   }
+  if (!sc) return;
   // statistics: thread t sums the keys t, t + 256, ...: one bin
   int64_t v = 0, a = 0;
   for (int k = threadIdx.x; k < keys; k += kBlock) {
@@ -254,7 +256,12 @@ __global__ void __launch_bounds__(kBlock) k_plan_fill(Frontier f, PlanKeys pk, P
     }
   }
   affected = wave_sum_i64(affected);
-  if (lane_id() == 0 && affected) stat_add(sc, ST_AFFECTED, affected);
+  if (lane_id() == 0 && affected) {
+    if (sc)
+      stat_add(sc, ST_AFFECTED, affected);
+    else
+      atomicAdd(&p.tail[PT_AFFECTED], static_cast<int32_t>(affected));
+  }
 }
 
 // Hub rows of sub-round blockIdx.x: table offsets (each sub-round uses the
@@ -363,45 +370,35 @@ __global__ void __launch_bounds__(kBlock) k_plan_hubs(PlanBuf p, PlanLists L, in
 
 }  // namespace
 
-PlanBuf plan_buf(const Workspace& ws) {
-  // the record buffer of the deferred totals: read back by the host, and by
-  // the plan's kernels, before the first scan of the iteration writes records
-  char* q = reinterpret_cast<char*>(ws.hot);
-  auto take = [&](size_t bytes) {
-    char* r = q;
-    q += (bytes + 255) & ~size_t(255);
-    return r;
-  };
-  static_assert(sizeof(HotRec) * kHotRegions * kHotCap >= 64 * 1024, "plan counters do not fit the record buffer");
+PlanBuf plan_buf(void* mem) {
   PlanBuf p;
-  int32_t* host = reinterpret_cast<int32_t*>(take(4 * kPlanHost));
-  p.cnt = host;
-  p.hub_ubase = host + kPlanKeys;
+  p.cnt = static_cast<int32_t*>(mem);
+  p.hub_ubase = p.cnt + kPlanKeys;
   p.hub_units = p.hub_ubase + kPlanRounds;
   p.hub_cbase = p.hub_units + kPlanRounds;
   p.hub_cunits = p.hub_cbase + kPlanRounds;
   p.hub_first = p.hub_cunits + kPlanRounds;
   p.tail = p.hub_first + kPlanRounds;
-  p.cursor = reinterpret_cast<int32_t*>(take(4 * kPlanKeys));
-  p.arcs = reinterpret_cast<int64_t*>(take(8 * kPlanKeys));
+  p.arcs = reinterpret_cast<int64_t*>(static_cast<char*>(mem) + kPlanArcs);
+  p.cursor = reinterpret_cast<int32_t*>(p.arcs + kPlanKeys);
   return p;
 }
 
-void launch_plan(const MoveArgs& a, Workspace& ws, const PlanKeys& pk, TimerPair* tb, TimerPair* th, hipStream_t st) {
-  const PlanBuf p = plan_buf(ws);
-  Frontier f{const_cast<uint32_t*>(a.cur), a.range, a.g.row_len, a.g.n, a.wave_max};
+void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* tb, TimerPair* th, hipStream_t st) {
+  const PlanBuf p = plan_buf(a.mem);
+  const Frontier f{a.cur, a.range, a.row_len, a.n, a.wave_max};
   PlanLists L;
-  for (int b = 0; b < NBINS; ++b) L.list[b] = pk.rounds == 1 ? ws.bins[b] : ws.bins[0];
-  HubOut H{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
-  const int64_t tiles = (static_cast<int64_t>(a.g.n) + kPlanTile - 1) / kPlanTile;
+  for (int b = 0; b < NBINS; ++b) L.list[b] = pk.rounds == 1 ? a.list[b] : a.list[0];
+  const int64_t tiles = (static_cast<int64_t>(a.n) + kPlanTile - 1) / kPlanTile;
   const unsigned grid = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(tiles, 2048)));
-  hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, p, a.rc_next, a.sc_next, a.next_fl.cnt);
+  hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, p, a.rc_next, a.sc_next, a.next_cnt);
   hipLaunchKernelGGL(k_plan_count, dim3(grid), dim3(kBlock), 0, st, f, pk, p);
   hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kBlock), 0, st, pk, p, a.rc, a.sc);
   hipExtLaunchKernelGGL(k_plan_fill, dim3(grid), dim3(kBlock), 0, st, tb->start, tb->stop, 0, f, pk, p, L, a.ever,
                         a.sc);
-  hipExtLaunchKernelGGL(k_plan_hubs, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, th->start, th->stop,
-                        0, p, L, pk.rounds, a.g.row_len, H, ws.hub_kid, a.rc);
+  if (a.hub_kid)
+    hipExtLaunchKernelGGL(k_plan_hubs, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, th->start,
+                          th->stop, 0, p, L, pk.rounds, a.row_len, a.hub, a.hub_kid, a.rc);
 }
 
 }  // namespace lv
