@@ -19,6 +19,13 @@
 //   holes left by arcs that reached weight 0 with the surviving arcs of the
 //   row's tail (O(holes) per row, not O(row length); rows stay unsorted);
 //   append new arcs into the slack; update 2m.
+//
+// Both weight types use it (int32 with an exact 2m, float32 with an FP64 2m).
+// Measured for float32 weights against one thread per update that walks its
+// rows: apply and DF of 1000 updates on a 250,001-vertex power-law graph
+// 2660 -> 248 us (rows up to 10^4 arcs; the walk of one row by one lane bound it).
+#include <algorithm>
+
 #include "lv_internal.hpp"
 
 namespace lv {
@@ -66,10 +73,14 @@ __device__ __forceinline__ int32_t pair_find(const uint64_t* keys, uint32_t size
 // Endpoints of direction e: directions 2k, 2k+1 belong to deletion k
 // (k < nd), then 2(nd + k), 2(nd + k) + 1 to insertion k.  Direction
 // 2k is the arc u -> v, 2k + 1 the arc v -> u.
+// W: int32_t, or float (the paper's precision).
+template <class W>
 struct Upd {
-  const int32_t *du, *dv, *dw;
+  const int32_t *du, *dv;
+  const W* dw;
   int64_t nd;
-  const int32_t *iu, *iv, *iw;
+  const int32_t *iu, *iv;
+  const W* iw;
   int64_t ni;
   __device__ __forceinline__ bool is_del(int64_t e) const { return e < 2 * nd; }
   __device__ __forceinline__ int64_t update(int64_t e) const { return e >> 1; }  // index into [del | ins]
@@ -80,11 +91,38 @@ struct Upd {
     a = (e & 1) ? y : x;
     c = (e & 1) ? x : y;
   }
-  __device__ __forceinline__ int32_t weight(int64_t e) const {
+  __device__ __forceinline__ W weight(int64_t e) const {
     const int64_t k = e >> 1;
     return k < nd ? dw[k] : iw[k - nd];
   }
 };
+
+__device__ __forceinline__ bool usable(int32_t x) { return x > 0; }
+__device__ __forceinline__ bool usable(float x) { return isfinite(x) && x > 0.0f; }
+
+// Weight totals: whole numbers, or FP64 sums in the same counter slots.
+__device__ __forceinline__ int64_t as_total(int32_t x) { return x; }
+__device__ __forceinline__ double as_total(float x) { return static_cast<double>(x); }
+__device__ __forceinline__ double block_total(double v, double* lds) {
+  for (int s = 32; s > 0; s >>= 1) v += __shfl_xor(v, s);
+  if (lane_id() == 0) lds[threadIdx.x / kWave] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < kBlock / kWave; ++w) t += lds[w];
+  __syncthreads();
+  return t;
+}
+__device__ __forceinline__ int64_t block_total(int64_t v, int64_t* lds) { return block_sum(v, lds); }
+__device__ __forceinline__ void total_add(int64_t* sc, int st, int64_t v) { stat_add(sc, st, v); }
+__device__ __forceinline__ void total_add(int64_t* sc, int st, double v) {
+  atomicAdd(reinterpret_cast<double*>(&sc[(blockIdx.x % kStatReplicas) * kStatStride + st]), v);
+}
+template <class T>
+__device__ __forceinline__ T total_of(const int64_t* sc, int st) {
+  T v = 0;
+  for (int r = 0; r < kStatReplicas; ++r) v += reinterpret_cast<const T*>(sc)[r * kStatStride + st];
+  return v;
+}
 
 __device__ __forceinline__ bool failed(const int64_t* ctr) {
   return *reinterpret_cast<const volatile int64_t*>(&ctr[CTR_ERR]) != 0;
@@ -114,28 +152,32 @@ __global__ void k_init(BatchScratch b, int64_t words, int64_t* __restrict__ ctr)
 // under the first direction that reaches it: row_slot[vertex] = that
 // direction's index e, row_of[e] = vertex (-1 for every other direction).
 constexpr uint64_t kTagMul = 2654435761ull;  // a prime above any tag bit count
-__global__ void __launch_bounds__(kBlock) k_validate(Upd U, int32_t n, BatchScratch b, int64_t* __restrict__ ctr,
+template <class W>
+__global__ void __launch_bounds__(kBlock) k_validate(Upd<W> U, int32_t n, BatchScratch b, int64_t* __restrict__ ctr,
                                                     uint64_t tag_bits) {
-  __shared__ int64_t lds[kBlock / kWave];
-  int64_t si = 0, sd = 0;
+  using T = decltype(as_total(W()));
+  __shared__ T lds[kBlock / kWave];
+  T si = 0, sd = 0;
   const int64_t total = U.nd + U.ni;
   for (int64_t k = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; k < total;
        k += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     const bool del = k < U.nd;
     const int32_t a = del ? U.du[k] : U.iu[k - U.nd];
     const int32_t c = del ? U.dv[k] : U.iv[k - U.nd];
-    const int32_t x = del ? U.dw[k] : U.iw[k - U.nd];
-    bool ok = a >= 0 && c >= 0 && a < n && c < n && a != c && x > 0;
+    const W x = del ? U.dw[k] : U.iw[k - U.nd];
+    bool ok = a >= 0 && c >= 0 && a < n && c < n && a != c && usable(x);
     int32_t h = -1;
     if (ok) {
       h = static_cast<int32_t>(pair_insert(b.keys, b.size, canon(a, c)));
-      if (atomicCAS(del ? &b.dw[h] : &b.iw[h], 0, x) != 0) ok = false;  // pair repeated on this side
+      int32_t bits;  // (a usable weight has no zero representation)
+      __builtin_memcpy(&bits, &x, sizeof(bits));
+      if (atomicCAS(del ? &b.dw[h] : &b.iw[h], 0, bits) != 0) ok = false;  // pair repeated on this side
     }
     if (ok) {
       if (del)
-        sd += x;
+        sd += as_total(x);
       else
-        si += x;
+        si += as_total(x);
     } else {
       set_error(ctr, LV_EINVAL);
       h = -1;
@@ -161,16 +203,17 @@ __global__ void __launch_bounds__(kBlock) k_validate(Upd U, int32_t n, BatchScra
       b.row_of[e] = head;
     }
   }
-  si = block_sum(si, lds);
-  sd = block_sum(sd, lds);
+  si = block_total(si, lds);
+  sd = block_total(sd, lds);
   if (threadIdx.x == 0) {  // (replicated counters: one address per workgroup would serialise)
-    if (si) stat_add(ctr + CTR_STATS0, ST_W_INS, si);
-    if (sd) stat_add(ctr + CTR_STATS0, ST_W_DEL, sd);
+    if (si != 0) total_add(ctr + CTR_STATS0, ST_W_INS, si);
+    if (sd != 0) total_add(ctr + CTR_STATS0, ST_W_DEL, sd);
   }
 }
 
 // rank of every direction among the directions of its row
-__global__ void k_rank(Upd U, BatchScratch b) {
+template <class W>
+__global__ void k_rank(Upd<W> U, BatchScratch b) {
   const int64_t dirs = 2 * (U.nd + U.ni);
   for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < dirs;
        e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -243,7 +286,8 @@ __global__ void __launch_bounds__(kBlock) k_rows(const int64_t* __restrict__ row
   }
 }
 
-__global__ void k_place(Upd U, BatchScratch b) {
+template <class W>
+__global__ void k_place(Upd<W> U, BatchScratch b) {
   const int64_t dirs = 2 * (U.nd + U.ni);
   for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < dirs;
        e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -319,7 +363,8 @@ __global__ void __launch_bounds__(kBlock) k_scan(const int64_t* __restrict__ row
 
 // Deletions must find their arc with enough weight; insertions merge into
 // an arc that survives the deletions, else append.
-__global__ void k_check(Upd U, const int32_t* __restrict__ wt, BatchScratch b, int64_t* __restrict__ ctr) {
+template <class W>
+__global__ void k_check(Upd<W> U, const W* __restrict__ wt, BatchScratch b, int64_t* __restrict__ ctr) {
   const int64_t dirs = 2 * (U.nd + U.ni);
   for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < dirs;
        e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -329,24 +374,25 @@ __global__ void k_check(Upd U, const int32_t* __restrict__ wt, BatchScratch b, i
     U.ends(e, a, c);
     const int64_t p = b.pos[2 * static_cast<int64_t>(h) + (a > c ? 1 : 0)];
     const int32_t r = b.row_slot[a];
-    const int32_t dwh = b.dw[h];
+    const W dwh = reinterpret_cast<const W*>(b.dw)[h];
     if (U.is_del(e)) {
       if (p < 0 || wt[p] < dwh) {
         set_error(ctr, LV_ENOEDGE);
         continue;
       }
-      if (wt[p] == dwh) atomicAdd(&b.r_zero[r], 1);
+      if (!(wt[p] - dwh > 0)) atomicAdd(&b.r_zero[r], 1);
     } else {
-      const bool merge = p >= 0 && !(dwh > 0 && dwh == wt[p]);
+      const bool merge = p >= 0 && !(dwh > 0 && !(wt[p] - dwh > 0));
       b.kind[e - 2 * U.nd] = merge ? 1 : 0;
       if (!merge) atomicAdd(&b.r_app[r], 1);
     }
   }
 }
 
+// two_m: null where 2m has no bound (float weights)
 __global__ void k_capacity(const int64_t* __restrict__ row_start, const int64_t* __restrict__ two_m, BatchScratch b,
                            int64_t* __restrict__ ctr) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+  if (two_m && blockIdx.x == 0 && threadIdx.x == 0) {
     const int64_t nm = *two_m + 2 * stat_total(ctr + CTR_STATS0, ST_W_INS) - 2 * stat_total(ctr + CTR_STATS0, ST_W_DEL);
     if (nm >= (int64_t(1) << 31)) set_error(ctr, LV_EOVERFLOW);
   }
@@ -361,11 +407,16 @@ __global__ void k_capacity(const int64_t* __restrict__ row_start, const int64_t*
 
 // ---- phase 2 ---------------------------------------------------------------
 
-__global__ void k_apply(Upd U, int32_t* __restrict__ wt, int64_t* __restrict__ two_m, BatchScratch b,
+// A pair that is deleted in part and merged back is updated by its
+// deletion, in that order; every arc has one writer.
+template <class W, class T>
+__global__ void k_apply(Upd<W> U, W* __restrict__ wt, T* __restrict__ two_m, BatchScratch b,
                         const int64_t* __restrict__ ctr) {
   if (failed(ctr)) return;
   if (blockIdx.x == 0 && threadIdx.x == 0)
-    *two_m += 2 * stat_total(ctr + CTR_STATS0, ST_W_INS) - 2 * stat_total(ctr + CTR_STATS0, ST_W_DEL);
+    *two_m += 2 * (total_of<T>(ctr + CTR_STATS0, ST_W_INS) - total_of<T>(ctr + CTR_STATS0, ST_W_DEL));
+  const W* dw = reinterpret_cast<const W*>(b.dw);
+  const W* iw = reinterpret_cast<const W*>(b.iw);
   const int64_t dirs = 2 * (U.nd + U.ni);
   for (int64_t e = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; e < dirs;
        e += static_cast<int64_t>(gridDim.x) * blockDim.x) {
@@ -373,10 +424,12 @@ __global__ void k_apply(Upd U, int32_t* __restrict__ wt, int64_t* __restrict__ t
     int32_t a, c;
     U.ends(e, a, c);
     const int64_t p = b.pos[2 * static_cast<int64_t>(h) + (a > c ? 1 : 0)];
-    if (U.is_del(e))
-      atomicSub(&wt[p], U.weight(e));  // a pair deleted and merged back gets two updates
-    else if (b.kind[e - 2 * U.nd])
-      atomicAdd(&wt[p], U.weight(e));
+    if (U.is_del(e)) {
+      const W left = wt[p] - dw[h];
+      wt[p] = left > 0 ? left + iw[h] : W(0);  // (iw is 0 without an insertion)
+    } else if (b.kind[e - 2 * U.nd] && dw[h] == 0) {
+      wt[p] += iw[h];
+    }
   }
 }
 
@@ -386,10 +439,12 @@ __global__ void k_apply(Upd U, int32_t* __restrict__ wt, int64_t* __restrict__ t
 // the row's partner range (zeroed <= partners).  A lane handles a row whose
 // tail is short; longer tails take the whole wavefront.
 constexpr int kTailLane = 16;
+template <class W>
 __global__ void __launch_bounds__(kBlock) k_tail(const int64_t* __restrict__ row_start, int32_t* __restrict__ row_len,
-                                                 const int32_t* __restrict__ col, const int32_t* __restrict__ wt,
+                                                 const int32_t* __restrict__ col, const W* __restrict__ wt,
                                                  BatchScratch b, const int64_t* __restrict__ ctr) {
   if (failed(ctr)) return;
+  W* tw = reinterpret_cast<W*>(b.tw);
   const int lane = lane_id();
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * (kBlock / kWave);
   for (int64_t s0 = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) / kWave * kWave; s0 < b.dirs;
@@ -402,10 +457,10 @@ __global__ void __launch_bounds__(kBlock) k_tail(const int64_t* __restrict__ row
       const int64_t s = row_start[a];
       int64_t q = b.r_pbase[e];
       for (int32_t k = Lp; k < L; ++k) {
-        const int32_t x = wt[s + k];
+        const W x = wt[s + k];
         if (x > 0) {
           b.tcol[q] = col[s + k];
-          b.tw[q] = x;
+          tw[q] = x;
           ++q;
         }
       }
@@ -425,7 +480,7 @@ __global__ void __launch_bounds__(kBlock) k_tail(const int64_t* __restrict__ row
         if (keep) {
           const int64_t q = base + out + __popcll(km & ((1ull << lane) - 1ull));
           b.tcol[q] = col[s + k];
-          b.tw[q] = wt[s + k];
+          tw[q] = wt[s + k];
         }
         out += __popcll(km);
       }
@@ -436,8 +491,9 @@ __global__ void __launch_bounds__(kBlock) k_tail(const int64_t* __restrict__ row
 
 // Zeroed head arcs take the row's tail survivors; insertions that do not
 // merge are appended after the (cut) row.
-__global__ void k_fill(Upd U, const int64_t* __restrict__ row_start, int32_t* __restrict__ row_len,
-                       int32_t* __restrict__ col, int32_t* __restrict__ wt, BatchScratch b,
+template <class W>
+__global__ void k_fill(Upd<W> U, const int64_t* __restrict__ row_start, int32_t* __restrict__ row_len,
+                       int32_t* __restrict__ col, W* __restrict__ wt, BatchScratch b,
                        const int64_t* __restrict__ ctr) {
   if (failed(ctr)) return;
   const int64_t dirs = 2 * (U.nd + U.ni);
@@ -454,7 +510,7 @@ __global__ void k_fill(Upd U, const int64_t* __restrict__ row_start, int32_t* __
       if (p - s >= Lp || wt[p] != 0) continue;  // tail arc, or weight left
       const int32_t j = atomicAdd(&b.r_hole[r], 1);
       col[p] = b.tcol[b.r_pbase[r] + j];
-      wt[p] = b.tw[b.r_pbase[r] + j];
+      wt[p] = reinterpret_cast<const W*>(b.tw)[b.r_pbase[r] + j];
     } else if (!b.kind[e - 2 * U.nd]) {
       const int64_t q = s + atomicAdd(&row_len[a], 1);
       col[q] = c;
@@ -463,45 +519,76 @@ __global__ void k_fill(Upd U, const int64_t* __restrict__ row_start, int32_t* __
   }
 }
 
-Upd upd(const lv_edges& del, const lv_edges& ins) {
-  return Upd{del.u, del.v, del.w, del.count, ins.u, ins.v, ins.w, ins.count};
-}
-
-}  // namespace
-
-int64_t batch_chunks_bound(int64_t dirs, int64_t cap) { return dirs + cap / kChunk + 1; }
-
-void launch_batch_phase1(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b,
-                         int64_t words, int64_t* ctr, hipStream_t st) {
-  const Upd U = upd(del, ins);
+// The whole edit; W, T: weights and 2m.  `bound`: 2m where it must stay
+// below 2^31, else null.
+template <class W, class T, class E>
+void launch_edit(const int64_t* row_start, int32_t* row_len, int32_t* col, W* w, T* two_m, const int64_t* bound,
+                 int32_t n, const E& del, const E& ins, const BatchScratch& b, int64_t words, int64_t* ctr,
+                 hipStream_t st) {
+  const Upd<W> U{del.u, del.v, del.w, del.count, ins.u, ins.v, ins.w, ins.count};
   const int64_t total = del.count + ins.count, dirs = 2 * total;
+  // phase 1
   hipLaunchKernelGGL(k_init, dim3(grid_for(std::max<int64_t>(std::max<int64_t>(b.size, dirs), words), kBlock, 2048)),
                      dim3(kBlock), 0, st, b, words, ctr);
-  hipLaunchKernelGGL(k_validate, dim3(grid_for(total, kBlock, 256)), dim3(kBlock), 0, st, U, g.n, b, ctr,
+  hipLaunchKernelGGL(k_validate<W>, dim3(grid_for(total, kBlock, 256)), dim3(kBlock), 0, st, U, n, b, ctr,
                      static_cast<uint64_t>(words) * 32);
-  hipLaunchKernelGGL(k_rank, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, b);
-  hipLaunchKernelGGL(k_rows, dim3(grid_for(dirs, kBlock * kRowsPer, 4096)), dim3(kBlock), 0, st, g.row_start,
-                     g.row_len, b, ctr);
-  hipLaunchKernelGGL(k_place, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, b);
+  hipLaunchKernelGGL(k_rank<W>, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, b);
+  hipLaunchKernelGGL(k_rows, dim3(grid_for(dirs, kBlock * kRowsPer, 4096)), dim3(kBlock), 0, st, row_start, row_len, b,
+                     ctr);
+  hipLaunchKernelGGL(k_place<W>, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, b);
   // chunks: one per touched row plus one per kChunk arcs of long rows; the
   // grid covers a few per touched row and strides over the rest
   hipLaunchKernelGGL(k_scan, dim3(grid_for(std::min<int64_t>(4 * dirs + 64, 32768) * kWave, kBlock, 8192)),
-                     dim3(kBlock), 0, st, g.row_start, g.col, b, ctr);
-  hipLaunchKernelGGL(k_check, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, g.w, b, ctr);
-  hipLaunchKernelGGL(k_capacity, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, g.row_start, g.two_m, b,
-                     ctr);
+                     dim3(kBlock), 0, st, row_start, col, b, ctr);
+  hipLaunchKernelGGL(k_check<W>, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, w, b, ctr);
+  hipLaunchKernelGGL(k_capacity, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, row_start, bound, b, ctr);
+  // phase 2 (does nothing if phase 1 set an error)
+  hipLaunchKernelGGL((k_apply<W, T>), dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, w, two_m, b, ctr);
+  if (del.count)
+    hipLaunchKernelGGL(k_tail<W>, dim3(grid_for(dirs, kBlock, 1024)), dim3(kBlock), 0, st, row_start, row_len, col, w,
+                       b, ctr);
+  hipLaunchKernelGGL(k_fill<W>, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, row_start, row_len, col, w,
+                     b, ctr);
 }
 
-void launch_batch_phase2(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b,
-                         int64_t* ctr, hipStream_t st) {
-  const Upd U = upd(del, ins);
-  const int64_t dirs = 2 * (del.count + ins.count);
-  hipLaunchKernelGGL(k_apply, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, g.w, g.two_m, b, ctr);
-  if (del.count)
-    hipLaunchKernelGGL(k_tail, dim3(grid_for(dirs, kBlock, 1024)), dim3(kBlock), 0, st, g.row_start,
-                       g.row_len, g.col, g.w, b, ctr);
-  hipLaunchKernelGGL(k_fill, dim3(grid_for(dirs, kBlock, 4096)), dim3(kBlock), 0, st, U, g.row_start, g.row_len,
-                     g.col, g.w, b, ctr);
+size_t al(size_t x) { return (x + 255) & ~size_t(255); }
+
+}  // namespace
+
+size_t carve_batch(BatchScratch& b, void* mem, int64_t nd, int64_t ni, int64_t cap) {
+  const int64_t U = nd + ni, E = 2 * U;
+  uint32_t size = 16;
+  while (size < 2 * U + 2) size <<= 1;
+  b.size = size;
+  b.dirs = E;
+  char* p = static_cast<char*>(mem);
+  size_t total = 0;
+  auto take = [&](size_t bytes) {
+    char* q = p ? p + total : nullptr;
+    total += al(bytes);
+    return q;
+  };
+  b.keys = reinterpret_cast<uint64_t*>(take(8ull * b.size));
+  b.dw = reinterpret_cast<int32_t*>(take(4ull * b.size));
+  b.iw = reinterpret_cast<int32_t*>(take(4ull * b.size));
+  b.pos = reinterpret_cast<int64_t*>(take(16ull * b.size));
+  b.slot = reinterpret_cast<int32_t*>(take(4ull * U));
+  int32_t** per_dir[11] = {&b.row_of, &b.r_len,  &b.r_cnt, &b.r_pbase, &b.r_zero, &b.r_app,
+                           &b.r_hole, &b.d_rank, &b.part,  &b.tcol,    &b.tw};
+  for (int k = 0; k < 11; ++k) *per_dir[k] = reinterpret_cast<int32_t*>(take(4ull * E));
+  b.kind = reinterpret_cast<int32_t*>(take(8ull * ni + 4));
+  b.chunk = reinterpret_cast<BatchScratch::Chunk*>(take(sizeof(BatchScratch::Chunk) * (E + cap / kChunk + 1)));
+  return total;
+}
+
+void launch_batch(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b, int64_t words,
+                  int64_t* ctr, hipStream_t st) {
+  launch_edit<int32_t, int64_t>(g.row_start, g.row_len, g.col, g.w, g.two_m, g.two_m, g.n, del, ins, b, words, ctr, st);
+}
+
+void launch_batch_f(const lv_graph_f& g, const lv_edges_f& del, const lv_edges_f& ins, const BatchScratch& b,
+                    int64_t words, int64_t* ctr, hipStream_t st) {
+  launch_edit<float, double>(g.row_start, g.row_len, g.col, g.w, g.two_m, nullptr, g.n, del, ins, b, words, ctr, st);
 }
 
 }  // namespace lv

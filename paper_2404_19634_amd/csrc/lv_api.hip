@@ -1102,44 +1102,15 @@ namespace {
 // device by the error slot) without waiting.  Host-side failures only.
 lv_status enqueue_batch(lv_graph* g, const lv_edges* del, const lv_edges* ins, Workspace& ws, hipStream_t st) {
   if (del->count + ins->count == 0) return LV_OK;
-  const int64_t U = del->count + ins->count, E = 2 * U;
   BatchScratch b;
-  b.size = static_cast<int64_t>(pow2_at_least(2 * U + 2));
-  b.dirs = E;
-  const int64_t chunks = batch_chunks_bound(E, g->cap);
-  size_t need = 0;
-  auto room = [&](size_t bytes) { need += align_up(bytes); };
-  room(8ull * b.size);
-  room(4ull * b.size);
-  room(4ull * b.size);
-  room(16ull * b.size);
-  room(4ull * U);
-  for (int k = 0; k < 11; ++k) room(4ull * E);
-  room(8ull * ins->count + 4);
-  room(sizeof(BatchScratch::Chunk) * chunks);
-  if (need > static_cast<size_t>(ws.pool_slots) * 4) return fail(LV_EWORKSPACE, "batch too large for the workspace pool");
-  char* p = reinterpret_cast<char*>(ws.pool_keys);
-  auto grab = [&](size_t bytes) {
-    char* q = p;
-    p += align_up(bytes);
-    return q;
-  };
-  b.keys = reinterpret_cast<uint64_t*>(grab(8ull * b.size));
-  b.dw = reinterpret_cast<int32_t*>(grab(4ull * b.size));
-  b.iw = reinterpret_cast<int32_t*>(grab(4ull * b.size));
-  b.pos = reinterpret_cast<int64_t*>(grab(16ull * b.size));
-  b.slot = reinterpret_cast<int32_t*>(grab(4ull * U));
-  int32_t** per_dir[11] = {&b.row_of, &b.r_len,  &b.r_cnt, &b.r_pbase, &b.r_zero, &b.r_app,
-                           &b.r_hole, &b.d_rank, &b.part,  &b.tcol,    &b.tw};
-  for (int k = 0; k < 11; ++k) *per_dir[k] = reinterpret_cast<int32_t*>(grab(4ull * E));
-  b.kind = reinterpret_cast<int32_t*>(grab(8ull * ins->count + 4));
-  b.chunk = reinterpret_cast<BatchScratch::Chunk*>(grab(sizeof(BatchScratch::Chunk) * chunks));
+  if (carve_batch(b, nullptr, del->count, ins->count, g->cap) > static_cast<size_t>(ws.pool_slots) * 4)
+    return fail(LV_EWORKSPACE, "batch too large for the workspace pool");
+  carve_batch(b, ws.pool_keys, del->count, ins->count, g->cap);
   b.tag = ws.dE;
   b.row_slot = ws.ccount;
   // phase 2 is gated on the device by the error slot, so the whole update
   // is enqueued at once and the host waits a single time
-  launch_batch_phase1(*g, *del, *ins, b, ws.words, ws.ctr, st);
-  launch_batch_phase2(*g, *del, *ins, b, ws.ctr, st);
+  launch_batch(*g, *del, *ins, b, ws.words, ws.ctr, st);
   LV_CHECK_LAUNCH();
   return LV_OK;
 }

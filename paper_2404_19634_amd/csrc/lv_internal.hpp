@@ -464,11 +464,14 @@ struct BatchScratch {
   int32_t* tcol;    // tail survivors, in the row's partner range (dirs entries)
   int32_t* tw;
 };
-int64_t batch_chunks_bound(int64_t dirs, int64_t cap);
-void launch_batch_phase1(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b,
-                         int64_t words, int64_t* ctr, hipStream_t st);
-void launch_batch_phase2(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b,
-                         int64_t* ctr, hipStream_t st);
+// Carves the scratch of a batch of nd + ni updates on a graph of capacity
+// `cap` out of mem and returns its bytes (mem null: the bytes only).  tag and
+// row_slot stay with the caller.
+size_t carve_batch(BatchScratch& b, void* mem, int64_t nd, int64_t ni, int64_t cap);
+void launch_batch(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b, int64_t words,
+                  int64_t* ctr, hipStream_t st);
+void launch_batch_f(const lv_graph_f& g, const lv_edges_f& del, const lv_edges_f& ins, const BatchScratch& b,
+                    int64_t words, int64_t* ctr, hipStream_t st);
 
 // mark.hip
 // updateWeights (Alg. 7); with df_frontier given it also marks DF's initial
