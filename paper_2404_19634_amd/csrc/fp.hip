@@ -1075,7 +1075,10 @@ lv_status enqueue_edit(const FWs& w, const lv_graph_f& g, const lv_edges_f& del,
   carve_batch(b, reinterpret_cast<char*>(w.pkeys) + kEditCtrBytes, del.count, ins.count, g.cap);
   b.tag = w.ever;
   b.row_slot = w.list[FB_WAVE];
-  launch_batch_f(g, del, ins, b, w.words, edit_counters(w), st);
+  if (del.count + ins.count <= kSmallUpdates)
+    launch_small_batch_f(g, del, ins, b, edit_counters(w), st);
+  else
+    launch_batch_f(g, del, ins, b, w.words, edit_counters(w), st);
   F_HIP(hipGetLastError());
   return LV_OK;
 }

@@ -94,6 +94,10 @@ thread_local Timer g_timer;
 
 }  // namespace
 
+// (a timed run launches the clear even where no row can need it, so that the
+// hook reports it)
+bool timing_hub_clear() { return !g_no_alloc && ((g_timed_mask.load() >> LV_TIME_HUB_CLEAR) & 1u); }
+
 TimerPair timer_pair(int kernel) {
   TimerPair p;
   if (g_no_alloc || !((g_timed_mask.load(std::memory_order_relaxed) >> kernel) & 1u)) return p;
@@ -173,6 +177,32 @@ lv_status read_counters(int64_t* host, const Workspace& ws, int count, hipStream
   LV_HIP(hipMemcpyAsync(host, ws.ctr, sizeof(int64_t) * count, hipMemcpyDeviceToHost, st));
   LV_HIP(hipStreamSynchronize(st));
   return LV_OK;
+}
+
+// The iteration's results (k_publish) in host[0, PUB_COUNT).
+lv_status publish(int64_t* host, const Workspace& ws, const int64_t* sc, hipStream_t st) {
+  if (!g_no_alloc) {  // pinned memory: the kernel writes it
+    launch_publish(ws, sc, host, st);
+  } else {
+    int64_t* tmp = reinterpret_cast<int64_t*>(ws.hot);  // (its records are applied)
+    launch_publish(ws, sc, tmp, st);
+    LV_HIP(hipMemcpyAsync(host, tmp, sizeof(int64_t) * PUB_COUNT, hipMemcpyDeviceToHost, st));
+  }
+  LV_HIP(hipGetLastError());
+  LV_HIP(hipStreamSynchronize(st));
+  return LV_OK;
+}
+
+// Milliseconds between two readings of the device clock.
+float clock_ms(int64_t a, int64_t b) {
+  static thread_local int khz = 0;  // (a constant of the hardware)
+  if (khz <= 0) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
+      return 0.f;
+  }
+  return static_cast<float>(b - a) / static_cast<float>(khz);
 }
 
 // A per-iteration statistic of one set, summed over its replicas.
@@ -449,18 +479,13 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
   pa.sc = a.sc;
   pa.sc_next = a.sc_next;
   pa.next_cnt = a.next_fl.cnt;
+  pa.stamp = a.stamp;
   pa.hub = HubOut{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
   pa.hub_kid = ws.hub_kid;
   launch_plan(pa, pk, &tb, &th, st);
-  ScanLists L{};
+  ScanLists L = single_round(ws, true, true);
   if (plan.size() == 1) {
-    for (int b = 0; b < NBINS; ++b) {
-      L.list[b] = ws.bins[b];
-      L.cnt[b] = -1;
-      S.bin_launches[b] += 1;
-    }
-    L.units = L.cunits = -1;
-    L.clear = true;
+    for (int b = 0; b < NBINS; ++b) S.bin_launches[b] += 1;
     launch_scan(a, ws, tu, L, bins_for_degrees(0, 0x7fffffff, a.wave_max), st);
     return LV_OK;
   }
@@ -507,9 +532,11 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
 // pass 0 with the state as it is (Alg. 4: renumber, aggregate, passes >= 1).
 // after_batch: a batch edit of the same batch was enqueued just before on
 // the stream, unread; its error (if any) is reported by this call.
+// edit: a small batch's edit is part of this call (scratch carved for it).
 lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const lv_edges* ins,
                       const lv_params* p, lv_state* state, void* wsp, size_t ws_bytes, lv_stats* stats,
-                      void* stream, int32_t resume_li = 0, bool after_batch = false) {
+                      void* stream, int32_t resume_li = 0, bool after_batch = false,
+                      const BatchScratch* edit = nullptr) {
   const auto t_start = std::chrono::steady_clock::now();
   if (!graph_ok(g)) return fail(LV_EINVAL, "invalid graph");
   if (!params_ok(p)) return fail(LV_EINVAL, "invalid parameters");
@@ -537,11 +564,18 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
   // The first kernel zeroes counters and frontier bitmasks and checks
   // 0 < 2m < 2^31 on the device; with 2m out of range every later kernel
   // leaves the state alone and the first readback reports the error.
-  LV_HIP(record(ev, 0, st));
   // fr_a's list is kept for DF's marking (and a resumed pass); the other
   // approaches fill the bitmask whole
   const bool dense_start = resume_li == 0 && ap != A_DF;
-  launch_call_begin(ws, g->two_m, dense_start, after_batch, st);
+  // A small batch starts in three launches (small.hip), with the frontier
+  // already in the degree bins where the first iteration is one sub-round.
+  const bool small = ap == A_DF && resume_li == 0 && !p->recompute_weights && D.count + I.count <= kSmallUpdates &&
+                     (edit || !after_batch);
+  const bool binned = small && sub_rounds(p->mode, 0, 2 * (D.count + I.count), N, tu).size() == 1;
+  if (small)
+    launch_small_df(*g, D, I, edit, *state, ws, binned, tu.wave_max_degree, st);
+  else
+    launch_call_begin(ws, g->two_m, dense_start, after_batch, st);
   LevelGraph L0;
   L0.n = N;
   L0.row_start = g->row_start;
@@ -595,7 +629,8 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       default:
         break;
     }
-    launch_update_weights(D, I, N, state->C, state->K, state->Sigma, df_frontier, front_list(ws, 0), ws.ctr, st);
+    if (!small)
+      launch_update_weights(D, I, N, state->C, state->K, state->Sigma, df_frontier, front_list(ws, 0), ws.ctr, st);
     if (p->recompute_weights) {
       // without auxiliary information (Section 4.2): K^t from the rows of
       // G^t and Sigma^t from C^{t-1}, replacing the incremental values
@@ -605,7 +640,6 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     if (p->swap_guard && !state->size) launch_community_sizes(state->C, N, ws.size, st);
   }
   LV_CHECK_LAUNCH();
-  LV_HIP(record(ev, 1, st));
 
   // ---- Alg. 4: passes of local-moving and aggregation --------------------
   LevelGraph L = L0;
@@ -621,11 +655,11 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
   bool moved_dirty = false;  // cleared by the first kernel, then by the SYNC apply unless pulled
   int64_t iter_seq = 0, round_seq = 0;  // select the alternating counter sets
   int64_t two_m = 0;
-  float ms_move = 0.f, ms_agg = 0.f;
+  float ms_mark = 0.f, ms_move = 0.f, ms_agg = 0.f;
   int64_t arcs_agg = 0;
   for (int32_t pass = 0; pass < p->max_passes; ++pass) {
-    LV_HIP(record(ev, 2, st));
     int32_t li = p->max_iterations;
+    float ms_pass = 0.f;
     MoveArgs a;
     a.g = L;
     a.C = Cl;
@@ -644,11 +678,11 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     if (pass == 0 && ap == A_DF) est_frontier = 2 * (D.count + I.count);
     if (pass == 0 && resume_li > 0) {
       li = resume_li;
-      LV_HIP(record(ev, 3, st));
     }
     for (int32_t it = 0; it < p->max_iterations && !(pass == 0 && resume_li > 0); ++it, ++iter_seq) {
       a.cur = cur;
       a.next = next;
+      a.stamp = it == 0 ? ws.ctr + CTR_T_MOVE : nullptr;
       a.cur_fl = cur_fl;
       a.next_fl = next_fl;
       // large frontiers pull the next frontier (reads) instead of pushing it
@@ -671,7 +705,10 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       // dense, or when there are many sub-rounds; a sparse frontier in a few
       // rounds is cheaper to pick from its list, with no readback in between
       // (a 16,000-update batch's two rounds: 10 us each, the readback 15).
-      const bool planned = !a.sparse || pass > 0 || plan.size() >= 8;
+      const bool in_bins = binned && pass == 0 && it == 0;  // (by the call's start)
+      const bool planned = !in_bins && (!a.sparse || pass > 0 || plan.size() >= 8);
+      // the hubs' neighbours matter to the next iteration only
+      const bool late_expand = !planned && plan.size() == 1;
       if (planned) {
         a.rc = ws.ctr + CTR_ROUND0 + (round_seq & 1) * kRoundSet;
         a.rc_next = ws.ctr + CTR_ROUND0 + ((round_seq + 1) & 1) * kRoundSet;
@@ -685,9 +722,13 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
         a.rc_next = ws.ctr + CTR_ROUND0 + ((round_seq + 1) & 1) * kRoundSet;
         a.sc = sc;
         a.sc_next = r == 0 ? sc_next : nullptr;
+        if (r > 0) a.stamp = nullptr;
         a.clear_cur = r + 1 == plan.size() ? 1 : 0;
         const uint32_t mask = bins_for_degrees(plan[r].deg_lo, plan[r].deg_hi, a.wave_max);
-        launch_round(a, ws, tu, plan[r], mask, st);
+        if (in_bins)  // (rows of over 2^20 arcs keep a table that has to be cleared)
+          launch_scan(a, ws, tu, single_round(ws, g->cap > kHubPartMaxDeg || timing_hub_clear(), !late_expand), mask, st);
+        else
+          launch_round(a, ws, tu, plan[r], mask, !late_expand, st);
         for (int b = 0; b < NBINS; ++b) S.bin_launches[b] += (mask >> b) & 1u;
       }
       if (p->mode == LV_SYNC) launch_apply_moves(a, ws, !pull, st);
@@ -698,20 +739,22 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       LV_CHECK_LAUNCH();
       std::swap(cur, next);
       std::swap(cur_fl, next_fl);
-      LV_HIP(record(ev, 3, st));
-      if ((s = read_counters(host, ws, CTR_ROUND0, st))) return s;
-      if (host[CTR_ERR])
-        return after_batch ? batch_error(host[CTR_ERR]) : device_error(host[CTR_ERR], "local-moving");
-      two_m = host[CTR_TWO_M];
-      const int64_t* hs = host + CTR_STATS0 + (iter_seq & 1) * kStatSet;
-      const int64_t movers = stat(hs, ST_MOVERS), gain = stat(hs, ST_GAIN);
-      est_frontier = stat(hs, ST_EXPAND);
+      if ((s = publish(host, ws, sc, st))) return s;
+      if (host[PUB_ERR]) return after_batch ? batch_error(host[PUB_ERR]) : device_error(host[PUB_ERR], "local-moving");
+      two_m = host[PUB_TWO_M];
+      const int64_t* hs = host + PUB_STATS;
+      const int64_t movers = hs[ST_MOVERS], gain = hs[ST_GAIN];
+      est_frontier = hs[ST_EXPAND];
       S.moves += movers;
-      S.arcs_scanned += stat(hs, ST_ARCS);
-      S.vertices_affected += stat(hs, ST_AFFECTED);
+      S.arcs_scanned += hs[ST_ARCS];
+      S.vertices_affected += hs[ST_AFFECTED];
       for (int b = 0; b < NBINS; ++b) {
-        S.bin_vertices[b] += stat(hs, ST_BIN_V0 + b);
-        S.bin_arcs[b] += stat(hs, ST_BIN_A0 + b);
+        S.bin_vertices[b] += hs[ST_BIN_V0 + b];
+        S.bin_arcs[b] += hs[ST_BIN_A0 + b];
+      }
+      if (!g_no_alloc) {  // (that entry point reports no times)
+        if (pass == 0 && it == 0) ms_mark = clock_ms(host[PUB_T_CALL], host[PUB_T_MOVE]);
+        ms_pass = clock_ms(host[PUB_T_MOVE], host[PUB_T_END]);
       }
       if (pass < LV_MAX_PASSES && it < LV_MAX_ITERS) {
         S.iter_moves[pass][it] = movers;
@@ -724,8 +767,10 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
         ++iter_seq;
         break;
       }
+      if (late_expand && it + 1 < p->max_iterations && hs[ST_BIN_V0 + BIN_HUB] > 0)
+        launch_hub_expand(a, ws, tu, single_round(ws, false, true), st);
     }
-    ms_move += ms_between(ev, 2, 3);
+    ms_move += ms_pass;
     S.passes = pass + 1;
     S.iterations[pass] = li;
     if (li <= 1) break;
@@ -775,7 +820,7 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     S.ms_other = ms_between(ev, 6, 7);
   }
   timer_collect(S.timed_launches, S.timed_ms);
-  S.ms_mark = ms_between(ev, 0, 1);
+  S.ms_mark = ms_mark;
   S.ms_move = ms_move;
   S.ms_aggregate = ms_agg;
   S.arcs_aggregated = arcs_agg;
@@ -1106,6 +1151,11 @@ lv_status enqueue_batch(lv_graph* g, const lv_edges* del, const lv_edges* ins, W
   if (carve_batch(b, nullptr, del->count, ins->count, g->cap) > static_cast<size_t>(ws.pool_slots) * 4)
     return fail(LV_EWORKSPACE, "batch too large for the workspace pool");
   carve_batch(b, ws.pool_keys, del->count, ins->count, g->cap);
+  if (del->count + ins->count <= kSmallUpdates) {
+    launch_small_batch(*g, *del, *ins, b, ws.ctr, st);
+    LV_CHECK_LAUNCH();
+    return LV_OK;
+  }
   b.tag = ws.dE;
   b.row_slot = ws.ccount;
   // phase 2 is gated on the device by the error slot, so the whole update
@@ -1165,6 +1215,15 @@ lv_status louvain_df_apply(lv_graph* g, const lv_edges* del, const lv_edges* ins
   Workspace ws;
   lv_status s = setup_ws(ws, g, wsp, ws_bytes);
   if (s) return s;
+  const int64_t updates = del->count + ins->count;
+  if (updates == 0) return run_louvain(A_DF, g, del, ins, p, state, wsp, ws_bytes, stats, stream);
+  if (updates <= kSmallUpdates) {  // the edit is part of DF's launches
+    BatchScratch b;
+    if (carve_batch(b, nullptr, del->count, ins->count, g->cap) > static_cast<size_t>(ws.pool_slots) * 4)
+      return fail(LV_EWORKSPACE, "batch too large for the workspace pool");
+    carve_batch(b, ws.pool_keys, del->count, ins->count, g->cap);
+    return run_louvain(A_DF, g, del, ins, p, state, wsp, ws_bytes, stats, stream, 0, true, &b);
+  }
   if ((s = enqueue_batch(g, del, ins, ws, static_cast<hipStream_t>(stream)))) return s;
   return run_louvain(A_DF, g, del, ins, p, state, wsp, ws_bytes, stats, stream, 0, true);
 }

@@ -49,6 +49,8 @@ constexpr int kHotRegions = 16;     // reservation counters of the deferred-tota
 constexpr int kRoundSet = (10 + kHotRegions) * kCtrLine;
 enum Ctr {
   CTR_ERR = 0 * kCtrLine,        // error code (first nonzero wins)
+  CTR_T_CALL = 1,                // device clock (wall_clock64): the call's first kernel began,
+  CTR_T_MOVE = 2,                // the pass's local-moving began
   CTR_TOTAL = 1 * kCtrLine,      // generic total (scans, counts)
   CTR_AUX0 = 2 * kCtrLine,
   CTR_AUX1 = 3 * kCtrLine,
@@ -108,6 +110,8 @@ enum Stat {
   NSTATS
 };
 static_assert(NSTATS <= kStatStride, "statistics exceed a replica");
+// What the last kernel of an iteration leaves for the host (k_publish).
+enum Pub { PUB_ERR = 0, PUB_TWO_M, PUB_T_CALL, PUB_T_MOVE, PUB_T_END, PUB_STATS, PUB_COUNT = PUB_STATS + NSTATS };
 constexpr int rc_bin(int b) { return RC_BIN0 + b * kCtrLine; }
 
 
@@ -473,6 +477,24 @@ void launch_batch(const lv_graph& g, const lv_edges& del, const lv_edges& ins, c
 void launch_batch_f(const lv_graph_f& g, const lv_edges_f& del, const lv_edges_f& ins, const BatchScratch& b,
                     int64_t words, int64_t* ctr, hipStream_t st);
 
+// k_scan: the touched rows' chunks, positions of the batch's arcs.
+void launch_batch_scan(const int64_t* row_start, const int32_t* col, int64_t updates, const BatchScratch& b,
+                       const int64_t* ctr, hipStream_t st);
+
+// small.hip -- batches of at most kSmallUpdates updates in three launches.
+// The scratch is carve_batch's (tag and row_slot are not used).
+constexpr int kSmallUpdates = 1024;
+void launch_small_batch(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch& b,
+                        int64_t* ctr, hipStream_t st);
+void launch_small_batch_f(const lv_graph_f& g, const lv_edges_f& del, const lv_edges_f& ins, const BatchScratch& b,
+                          int64_t* ctr, hipStream_t st);
+// DF's start of a call on a small batch, in place of launch_call_begin and
+// launch_update_weights; with b also the batch edit.  bin: the frontier goes
+// to ws.bins with the counters of the first sub-round, as its binning
+// would leave them; else to fr_a and its list.
+void launch_small_df(const lv_graph& g, const lv_edges& del, const lv_edges& ins, const BatchScratch* b,
+                     const lv_state& s, Workspace& ws, bool bin, int32_t wave_max, hipStream_t st);
+
 // mark.hip
 // updateWeights (Alg. 7); with df_frontier given it also marks DF's initial
 // frontier (Alg. 1) in the same pass.  Does nothing if ctr[CTR_ERR] is set;
@@ -558,6 +580,7 @@ struct MoveArgs {
   int64_t* rc_next;       // the other set, zeroed by this round's binning for the next round
   int64_t* sc;            // this iteration's statistics set
   int64_t* sc_next;       // the other set; zeroed by the first round's binning when non-null
+  int64_t* stamp;         // the iteration's first kernel leaves its start time here (or null)
   int32_t clear_cur;      // 1: binning clears the current frontier as it reads it (last round)
   int32_t sparse;         // 1: the scan may run as one fused launch (a frontier bound that is a small
                           // share of the level's vertices, or a small aggregated level)
@@ -619,6 +642,7 @@ struct PlanArgs {
   // counters of the integer path (null in the other: the host takes arcs
   // and PT_AFFECTED from the plan)
   int64_t *rc, *rc_next, *sc, *sc_next, *next_cnt;
+  int64_t* stamp;
   HubOut hub;
   int64_t* hub_kid;  // null: no hub units
 };
@@ -631,9 +655,13 @@ struct ScanLists {
   int32_t units, cunits;   // hub units (-1: likewise)
   int64_t hub_first, ubase, cbase;  // where the sub-round's hub items and units start
   bool clear;              // a hub row has a global table to clear
+  bool expand;             // moved hubs mark their neighbours now (else launch_hub_expand)
 };
 void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const ScanLists& s, uint32_t bin_mask,
                  hipStream_t st);
+void launch_hub_expand(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const ScanLists& s, hipStream_t st);
+// The lists of a single sub-round, whose counts are in its counters.
+ScanLists single_round(const Workspace& ws, bool clear, bool expand);
 
 // Measurement hook (lv_set_timing): the start and stop events of one launch
 // of a timed kernel, for hipExtLaunchKernelGGL, which stamps them with the
@@ -653,7 +681,7 @@ void timer_collect(int32_t* launches, double* ms);  // adds per kernel, resets
 // `bin_mask` (and hub inserts), hub decisions.  Four launches.
 uint32_t bins_for_degrees(int32_t lo, int32_t hi, int32_t wave_max);
 void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
-                  hipStream_t st);
+                  bool expand, hipStream_t st);
 void launch_apply_moves(const MoveArgs& a, Workspace& ws, bool clear_moved, hipStream_t st);
 void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st);
 // Host helpers shared with the paper-precision path (fp.hip): the error
@@ -671,6 +699,10 @@ std::vector<SubRound> lv_sub_rounds(int32_t mode, int32_t pass, int64_t est_fron
 // fr_a starts invalid (its bitmask is about to be filled without listing).
 void launch_call_begin(Workspace& ws, const int64_t* two_m, bool dense_a, bool keep_err, hipStream_t st);
 FrontList front_list(const Workspace& ws, int k);
+// End of an iteration: the error slot, 2m, the clocks and the statistics of
+// set sc, summed over the replicas, to dst (PUB_COUNT slots; device memory or
+// pinned host memory).
+void launch_publish(const Workspace& ws, const int64_t* sc, int64_t* dst, hipStream_t st);
 // Marks a frontier list invalid (its bitmask was filled without listing).
 void launch_list_invalid(const FrontList& f, hipStream_t st);
 

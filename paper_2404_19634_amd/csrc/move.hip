@@ -466,6 +466,7 @@ __global__ void k_call_begin(int64_t* __restrict__ ctr, uint32_t* __restrict__ f
   for (int64_t k = t0; k < CTR_COUNT; k += stride) {
     int64_t v = 0;
     if (k == CTR_TWO_M) v = *two_m;
+    if (k == CTR_T_CALL) v = static_cast<int64_t>(wall_clock64());
     if (k == CTR_FL0 && dense_a) v = kFlInvalid;
     if (k == CTR_ERR) {
       const int64_t t = *two_m;
@@ -473,6 +474,29 @@ __global__ void k_call_begin(int64_t* __restrict__ ctr, uint32_t* __restrict__ f
       v = prev ? prev : (t <= 0 ? LV_EEMPTY : (t >= kTwoMLimit ? LV_EOVERFLOW : 0));
     }
     ctr[k] = v;
+  }
+}
+
+// The last kernel of an iteration.  One workgroup sums the 32 replicas of
+// every statistic and writes the few values the host takes its decisions
+// from, with device clock readings for the phase times: 28 slots in place of
+// a copy of all counters (18 KB), and no event packets between the kernels
+// (four of them cost 20 us of an 83 us update).
+__global__ void __launch_bounds__(kBlock) k_publish(const int64_t* __restrict__ ctr, const int64_t* __restrict__ sc,
+                                                   int64_t* __restrict__ dst) {
+  static_assert(kStatReplicas == 32, "half a wavefront per statistic");
+  const int r = threadIdx.x % kStatReplicas;
+  for (int s = threadIdx.x / kStatReplicas; s < NSTATS; s += kBlock / kStatReplicas) {
+    int64_t v = sc[r * kStatStride + s];
+    for (int d = kStatReplicas / 2; d > 0; d >>= 1) v += __shfl_xor(v, d);
+    if (r == 0) dst[PUB_STATS + s] = v;
+  }
+  if (threadIdx.x == 0) {
+    dst[PUB_ERR] = ctr[CTR_ERR];
+    dst[PUB_TWO_M] = ctr[CTR_TWO_M];
+    dst[PUB_T_CALL] = ctr[CTR_T_CALL];
+    dst[PUB_T_MOVE] = ctr[CTR_T_MOVE];
+    dst[PUB_T_END] = static_cast<int64_t>(wall_clock64());
   }
 }
 
@@ -499,7 +523,8 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
                                                         int32_t clear_cur, Bins bins, HubOut H,
                                                         int64_t* __restrict__ rc, int64_t* __restrict__ sc,
                                                         int64_t* __restrict__ rc_next,
-                                                        int64_t* __restrict__ sc_next) {
+                                                        int64_t* __restrict__ sc_next, int64_t* __restrict__ stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) *stamp = static_cast<int64_t>(wall_clock64());
   __shared__ int32_t s_cnt[NBINS];
   __shared__ int64_t s_base[NBINS];
   __shared__ unsigned long long s_stat[kBinStats];  // block totals of the statistics
@@ -2029,6 +2054,10 @@ void launch_call_begin(Workspace& ws, const int64_t* two_m, bool dense_a, bool k
                      dense_a ? 1 : 0, keep_err ? 1 : 0);
 }
 
+void launch_publish(const Workspace& ws, const int64_t* sc, int64_t* dst, hipStream_t st) {
+  hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, st, ws.ctr, sc, dst);
+}
+
 FrontList front_list(const Workspace& ws, int k) {
   return FrontList{ws.fl[k], ws.ctr + CTR_FL0 + k * kFlSet, ws.fl_capr};
 }
@@ -2144,23 +2173,37 @@ void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const Sc
     const int bf = S.cnt[BIN_HUB] >= 0 ? grid_by_est(S.cnt[BIN_HUB], 4, 64) : 64;
     hipLaunchKernelGGL(k_hub_final, dim3(bf), dim3(kBlock), 0, st, D, hlist, ws.hub_cbase + S.hub_first,
                        ws.hub_cnum + S.hub_first, ws.unit_g, ws.unit_c, ws.hub_moved + S.hub_first, h_kid);
-    if (a.push)
-      hipLaunchKernelGGL(k_hub_expand, dim3(cap_grid(k_hub_expand, bu)), dim3(kBlock), 0, st, D, hlist, u_b, u_a,
-                         ws.hub_moved + S.hub_first);
+    if (S.expand) launch_hub_expand(a, ws, tu, S, st);
   }
 }
 
-void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
-                  hipStream_t st) {
-  const int64_t words = (static_cast<int64_t>(a.g.n) + 31) / 32;
-  Bins b;
+void launch_hub_expand(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const ScanLists& S, hipStream_t st) {
+  if (!a.push) return;
+  Dev D = make_dev(a, ws, tu);
+  D.units = S.units;
+  const int grid = grid_by_est(S.units >= 0 ? S.units : std::max<int64_t>(a.est, 1), 1, tu.blocks_hub);
+  hipLaunchKernelGGL(k_hub_expand, dim3(cap_grid(k_hub_expand, grid)), dim3(kBlock), 0, st, D, S.list[BIN_HUB],
+                     ws.u_ins_b + S.ubase, ws.u_ins_a + S.ubase, ws.hub_moved + S.hub_first);
+}
+
+ScanLists single_round(const Workspace& ws, bool clear, bool expand) {
   ScanLists S{};
   for (int k = 0; k < NBINS; ++k) {
-    b.list[k] = S.list[k] = ws.bins[k];
+    S.list[k] = ws.bins[k];
     S.cnt[k] = -1;
   }
   S.units = S.cunits = -1;
-  S.clear = true;
+  S.clear = clear;
+  S.expand = expand;
+  return S;
+}
+
+void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
+                  bool expand, hipStream_t st) {
+  const int64_t words = (static_cast<int64_t>(a.g.n) + 31) / 32;
+  Bins b;
+  for (int k = 0; k < NBINS; ++k) b.list[k] = ws.bins[k];
+  const ScanLists S = single_round(ws, true, expand);
   HubOut HO{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
   const TimerPair tb = timer_pair(LV_TIME_BINNING);
   // (a listed frontier has at most a.est vertices; a bitmask walk is a
@@ -2170,7 +2213,7 @@ void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const S
                         tb.stop, 0, const_cast<uint32_t*>(a.cur), a.cur_fl, a.sc_next ? a.next_fl.cnt : nullptr,
                         a.range, a.ever, a.g.row_len, a.g.n, a.wave_max,
                         r.hash_round, r.hash_shift, r.id_lo, r.id_hi, r.deg_lo, r.deg_hi, a.clear_cur, b, HO, a.rc,
-                        a.sc, a.rc_next, a.sc_next);
+                        a.sc, a.rc_next, a.sc_next, a.stamp);
   launch_scan(a, ws, tu, S, bin_mask, st);
 }
 

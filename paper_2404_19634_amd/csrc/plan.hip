@@ -96,7 +96,8 @@ __device__ __forceinline__ bool tile_keys(const Frontier& f, const PlanKeys& pk,
 // Counters of the plan, the other sub-round and statistics sets, and the
 // next frontier's list counts start from zero.
 __global__ void k_plan_begin(PlanBuf p, int64_t* __restrict__ rc_next, int64_t* __restrict__ sc_next,
-                             int64_t* __restrict__ next_cnt) {
+                             int64_t* __restrict__ next_cnt, int64_t* __restrict__ stamp) {
+  if (stamp && threadIdx.x == 0) *stamp = static_cast<int64_t>(wall_clock64());
   for (int k = threadIdx.x; k < kPlanKeys; k += blockDim.x) {
     p.cnt[k] = 0;
     p.arcs[k] = 0;
@@ -391,7 +392,8 @@ void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* tb, TimerPair
   for (int b = 0; b < NBINS; ++b) L.list[b] = pk.rounds == 1 ? a.list[b] : a.list[0];
   const int64_t tiles = (static_cast<int64_t>(a.n) + kPlanTile - 1) / kPlanTile;
   const unsigned grid = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(tiles, 2048)));
-  hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, p, a.rc_next, a.sc_next, a.next_cnt);
+  hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, p, a.rc_next, a.sc_next, a.next_cnt,
+                     a.stamp);
   hipLaunchKernelGGL(k_plan_count, dim3(grid), dim3(kBlock), 0, st, f, pk, p);
   hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kBlock), 0, st, pk, p, a.rc, a.sc);
   hipExtLaunchKernelGGL(k_plan_fill, dim3(grid), dim3(kBlock), 0, st, tb->start, tb->stop, 0, f, pk, p, L, a.ever,
