@@ -172,7 +172,7 @@ unsigned blocks_for(int32_t n) { return static_cast<unsigned>((static_cast<int64
 void launch_accumulate(const int32_t* C, int32_t n, const int32_t* v32, const int64_t* v64, int32_t* out_count,
                        int64_t* out_val, hipStream_t st) {
   if (n <= 0) return;
-  const int64_t blocks = (static_cast<int64_t>(n) + kAccBlock - 1) / kAccBlock;
+  const int64_t blocks = (static_cast<int64_t>(n) + kPerBlock - 1) / kPerBlock;
   hipLaunchKernelGGL(k_accumulate, dim3(static_cast<unsigned>(std::min<int64_t>(blocks, kAccMaxBlocks))),
                      dim3(kAccBlock), 0, st, C, n, v32, v64, out_count, out_val);
 }

@@ -988,6 +988,17 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
   const int64_t wave = (rb * blockDim.x + threadIdx.x) / kWave;
   const int64_t nwaves = nb * blockDim.x / kWave;
   int64_t gain_acc = 0, moved = 0, marcs = 0;
+  // A lane owns the slots it inserted: it reads their sums for the decision
+  // and clears them for the next row, so no pass over the table is made
+  // (converged rows hold a few communities in a table of twice their arcs).
+  // The whole table is cleared once, as far as the first pass may use it.
+  for (uint32_t t = lane; t < static_cast<uint32_t>(TS); t += kWave) {
+    keys[t] = -1;
+    vals[t] = 0;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   // the next row's id and metadata are loaded while this row is scanned
   int32_t n_i = 0, n_deg = 0, n_d = 0;
   int64_t n_start = 0;
@@ -1007,30 +1018,28 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
     if (idx + nwaves < count) n_i = list[idx + nwaves];
     // table of the smallest power of two >= 2*deg slots (at least 64)
     const uint32_t ts = max(64u, 1u << (32 - __clz(static_cast<uint32_t>(2 * deg - 1))));
-    for (uint32_t t = lane; t < ts; t += kWave) {
-      keys[t] = -1;
-      vals[t] = 0;
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     // a lane's arcs (deg <= TS/2): all loads, then all gathers, then the
     // table, so the memory latencies overlap instead of adding up
     constexpr int U = TS / (2 * kWave);
+    const int nu = __builtin_amdgcn_readfirstlane((deg + kWave - 1) / kWave);  // steps that hold arcs
     int32_t kid = 0;
+    int32_t cs[U], own[U];  // communities of the lane's arcs, and the slots it inserted
     {
-      int32_t js[U], xs[U], cs[U];
+      int32_t js[U], xs[U];
 #pragma unroll
       for (int q = 0; q < U; ++q) {
+        if (q >= nu) continue;
         const int32_t k = lane + q * kWave;
         js[q] = k < deg ? D.col[start + k] : i;
         xs[q] = k < deg ? D.wt[start + k] : 0;
       }
 #pragma unroll
-      for (int q = 0; q < U; ++q) cs[q] = js[q] != i ? D.C[js[q]] : d;
+      for (int q = 0; q < U; ++q)
+        if (q < nu) cs[q] = js[q] != i ? D.C[js[q]] : d;
 #pragma unroll
       for (int q = 0; q < U; ++q) {
-        if (js[q] == i) continue;
+        own[q] = -1;
+        if (q >= nu || js[q] == i) continue;
         if (cs[q] == d) {
           kid += xs[q];
           continue;
@@ -1040,6 +1049,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
           const int32_t old = atomicCAS(&keys[h], -1, cs[q]);
           if (old == -1 || old == cs[q]) {
             atomicAdd(&vals[h], xs[q]);
+            if (old == -1) own[q] = static_cast<int32_t>(h);
             break;
           }
           h = (h + 1) & (ts - 1);
@@ -1058,28 +1068,25 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
     const GainBar bar = gain_bar(two_m, kid, Ki, Sd);
     int64_t bg = LLONG_MIN;
     int32_t bc = INT_MAX;
-    // the table in chunks of kDecideSlots slots per lane (the gathers of a
-    // chunk overlap; the chunk bounds the registers the phase holds)
-    for (uint32_t t0 = 0; t0 < ts; t0 += kDecideSlots * kWave) {
-      int32_t cc[kDecideSlots], vv[kDecideSlots];
-      int64_t sg[kDecideSlots];
+    int32_t vv[U];
+    int64_t sg[U];
 #pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q) {
-        const uint32_t t = t0 + lane + q * kWave;
-        cc[q] = t < ts ? keys[t] : -1;
-        vv[q] = t < ts ? vals[t] : 0;
+    for (int q = 0; q < U; ++q)
+      if (q < nu) vv[q] = own[q] >= 0 ? vals[own[q]] : 0;
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (q < nu) sg[q] = own[q] >= 0 && bar.open(vv[q]) ? D.Sigma[cs[q]] : 0;
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (q >= nu || own[q] < 0) continue;
+      keys[own[q]] = -1;
+      vals[own[q]] = 0;
+      if (!bar.open(vv[q])) continue;
+      const int64_t g = gain_of(two_m, vv[q], kid, Ki, sg[q], Sd);
+      if (better(g, cs[q], bg, bc)) {
+        bg = g;
+        bc = cs[q];
       }
-#pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q) sg[q] = cc[q] >= 0 && bar.open(vv[q]) ? D.Sigma[cc[q]] : 0;
-#pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q)
-        if (cc[q] >= 0 && bar.open(vv[q])) {
-          const int64_t g = gain_of(two_m, vv[q], kid, Ki, sg[q], Sd);
-          if (better(g, cc[q], bg, bc)) {
-            bg = g;
-            bc = cc[q];
-          }
-        }
     }
     for (int s = 1; s < kWave; s <<= 1) {
       const int64_t og = __shfl_xor(bg, s);
@@ -1102,7 +1109,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
           front_mark(D.next, D.nl, j, j != i);
         }
     }
-    // the next row's table clear must not overtake this row's reads
+    // the next row's inserts must not overtake this row's clears
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1193,6 +1200,12 @@ __device__ __forceinline__ void role_block(const Dev& D, int64_t two_m, const in
                                            int64_t nb, int32_t* keys, int32_t* vals, Red* red) {
   const int64_t count = bin_count(D, BIN_BLOCK);
   int64_t gain_acc = 0, moved = 0, marcs = 0;
+  if (rb < count)
+    for (int t = threadIdx.x; t < kBlockTS; t += kBlock) {
+      keys[t] = -1;
+      vals[t] = 0;
+    }
+  __syncthreads();
   // the next row's id and metadata are loaded while this row is scanned
   // (no other workgroup changes C of a row this workgroup holds)
   int32_t n_i = 0, n_deg = 0, n_d = 0;
@@ -1212,16 +1225,16 @@ __device__ __forceinline__ void role_block(const Dev& D, int64_t two_m, const in
     const int64_t Sd = D.Sigma[d];
     if (idx + nb < count) n_i = list[idx + nb];
     const uint32_t ts = max(256u, 1u << (32 - __clz(static_cast<uint32_t>(2 * deg - 1))));
-    for (uint32_t t = threadIdx.x; t < ts; t += kBlock) {
-      keys[t] = -1;
-      vals[t] = 0;
-    }
-    __syncthreads();
-    // a thread's arcs and table slots are loaded, then gathered, in chunks
+    // a thread's arcs are loaded, then gathered, in chunks; it owns the
+    // slots it inserts (as in the wavefront role)
     constexpr int U = kDecideSlots;
+    constexpr int kOwn = kBlockMaxDegree / kBlock;
     int64_t kid = 0;
-    for (int32_t k0 = 0; k0 < deg; k0 += U * kBlock) {
-      int32_t js[U], xs[U], cs[U];
+    int32_t cs[kOwn], own[kOwn];
+#pragma unroll
+    for (int q0 = 0; q0 < kOwn; q0 += U) {
+      const int32_t k0 = q0 * kBlock;
+      int32_t js[U], xs[U];
 #pragma unroll
       for (int q = 0; q < U; ++q) {
         const int32_t k = k0 + threadIdx.x + q * kBlock;
@@ -1229,19 +1242,22 @@ __device__ __forceinline__ void role_block(const Dev& D, int64_t two_m, const in
         xs[q] = k < deg ? D.wt[start + k] : 0;
       }
 #pragma unroll
-      for (int q = 0; q < U; ++q) cs[q] = js[q] != i ? D.C[js[q]] : d;
+      for (int q = 0; q < U; ++q) cs[q0 + q] = js[q] != i ? D.C[js[q]] : d;
 #pragma unroll
       for (int q = 0; q < U; ++q) {
+        own[q0 + q] = -1;
         if (js[q] == i) continue;
-        if (cs[q] == d) {
+        const int32_t c = cs[q0 + q];
+        if (c == d) {
           kid += xs[q];
           continue;
         }
-        uint32_t h = hash_slot(static_cast<uint32_t>(cs[q]), ts);
+        uint32_t h = hash_slot(static_cast<uint32_t>(c), ts);
         while (true) {
-          const int32_t old = atomicCAS(&keys[h], -1, cs[q]);
-          if (old == -1 || old == cs[q]) {
+          const int32_t old = atomicCAS(&keys[h], -1, c);
+          if (old == -1 || old == c) {
             atomicAdd(&vals[h], xs[q]);
+            if (old == -1) own[q0 + q] = static_cast<int32_t>(h);
             break;
           }
           h = (h + 1) & (ts - 1);
@@ -1257,26 +1273,26 @@ __device__ __forceinline__ void role_block(const Dev& D, int64_t two_m, const in
     const GainBar bar = gain_bar(two_m, kid, Ki, Sd);
     int64_t bg = LLONG_MIN;
     int32_t bc = INT_MAX;
-    for (uint32_t t0 = 0; t0 < ts; t0 += kDecideSlots * kBlock) {
-      int32_t cc[kDecideSlots], vv[kDecideSlots];
-      int64_t sg[kDecideSlots];
 #pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q) {
-        const uint32_t t = t0 + threadIdx.x + q * kBlock;
-        cc[q] = t < ts ? keys[t] : -1;
-        vv[q] = t < ts ? vals[t] : 0;
-      }
+    for (int q0 = 0; q0 < kOwn; q0 += U) {
+      int32_t vv[U];
+      int64_t sg[U];
 #pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q) sg[q] = cc[q] >= 0 && bar.open(vv[q]) ? D.Sigma[cc[q]] : 0;
+      for (int q = 0; q < U; ++q) vv[q] = own[q0 + q] >= 0 ? vals[own[q0 + q]] : 0;
 #pragma unroll
-      for (int q = 0; q < kDecideSlots; ++q)
-        if (cc[q] >= 0 && bar.open(vv[q])) {
-          const int64_t g = gain_of(two_m, vv[q], kid, Ki, sg[q], Sd);
-          if (better(g, cc[q], bg, bc)) {
-            bg = g;
-            bc = cc[q];
-          }
+      for (int q = 0; q < U; ++q) sg[q] = own[q0 + q] >= 0 && bar.open(vv[q]) ? D.Sigma[cs[q0 + q]] : 0;
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (own[q0 + q] < 0) continue;
+        keys[own[q0 + q]] = -1;
+        vals[own[q0 + q]] = 0;
+        if (!bar.open(vv[q])) continue;
+        const int64_t g = gain_of(two_m, vv[q], kid, Ki, sg[q], Sd);
+        if (better(g, cs[q0 + q], bg, bc)) {
+          bg = g;
+          bc = cs[q0 + q];
         }
+      }
     }
     block_argmax(bg, bc, red->g, red->c);
     if (decide_move(D, d, bc, bg)) {
@@ -1336,6 +1352,11 @@ struct HubIn {
 __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, int64_t rb, int64_t nb, int32_t* tk,
                                                 int32_t* tv, int32_t* hist, Red* red) {
   const int64_t count = unit_count(D);
+  if (rb < count)
+    for (int s = threadIdx.x; s < kHubTS; s += kBlock) {
+      tk[s] = -1;
+      tv[s] = 0;
+    }
   for (int64_t u = rb; u < count; u += nb) {
     const int32_t h = H.u_b[u];
     const int32_t i = H.list[h];
@@ -1350,17 +1371,13 @@ __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, in
       continue;
     }
     unsigned long long* tab = H.tab + off;
-    for (int s = threadIdx.x; s < kHubTS; s += kBlock) {
-      tk[s] = -1;
-      tv[s] = 0;
-    }
-    __syncthreads();
+    __syncthreads();  // the table is clear
     const int64_t a0 = H.u_a[u];
     const int64_t a1 = min(static_cast<int64_t>(deg), a0 + kHubUnitArcs);
     int64_t kid = 0;
     // each thread's arcs: all loads first, then all gathers, then the table
     constexpr int kPer = kHubUnitArcs / kBlock;
-    int32_t js[kPer], xs[kPer], cs[kPer];
+    int32_t js[kPer], xs[kPer], cs[kPer], own[kPer];  // (own: slots this thread inserted)
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
       const int64_t a = a0 + threadIdx.x + static_cast<int64_t>(q) * kBlock;
@@ -1371,6 +1388,7 @@ __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, in
     for (int q = 0; q < kPer; ++q) cs[q] = js[q] != i ? D.C[js[q]] : d;
 #pragma unroll
     for (int q = 0; q < kPer; ++q) {
+      own[q] = -1;
       if (js[q] == i) continue;
       const int32_t c = cs[q], x = xs[q];
       if (c == d) {
@@ -1388,6 +1406,7 @@ __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, in
         const int32_t old = atomicCAS(&tk[p], -1, c);
         if (old == -1 || old == c) {
           atomicAdd(&tv[p], x);
+          if (old == -1) own[q] = static_cast<int32_t>(p);
           done = true;
           break;
         }
@@ -1404,18 +1423,23 @@ __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, in
       const int64_t ui = a0 / kHubUnitArcs;
       unsigned long long* pairs = tab + ui * kHubUnitArcs;
       int32_t* segoff = reinterpret_cast<int32_t*>(tab + 2 * static_cast<int64_t>(deg)) + ui * (ns + 1);
+      // (each thread handles the slots it inserted, and clears them)
       for (uint32_t q = threadIdx.x; q <= ns; q += kBlock) hist[q] = 0;
       __syncthreads();
-      for (int sl = threadIdx.x; sl < kHubTS; sl += kBlock)
-        if (tk[sl] >= 0) atomicAdd(&hist[hash_slot(static_cast<uint32_t>(tk[sl]), ns)], 1);
+#pragma unroll
+      for (int q = 0; q < kPer; ++q)
+        if (own[q] >= 0) atomicAdd(&hist[hash_slot(static_cast<uint32_t>(cs[q]), ns)], 1);
       __syncthreads();
       block_exscan(hist, static_cast<int>(ns), red->w);
       for (uint32_t q = threadIdx.x; q <= ns; q += kBlock) segoff[q] = hist[q];
       __syncthreads();
-      for (int sl = threadIdx.x; sl < kHubTS; sl += kBlock)
-        if (tk[sl] >= 0) {
-          const int32_t pos = atomicAdd(&hist[hash_slot(static_cast<uint32_t>(tk[sl]), ns)], 1);
-          pairs[pos] = pack_pair(tk[sl], tv[sl]);
+#pragma unroll
+      for (int q = 0; q < kPer; ++q)
+        if (own[q] >= 0) {
+          const int32_t pos = atomicAdd(&hist[hash_slot(static_cast<uint32_t>(cs[q]), ns)], 1);
+          pairs[pos] = pack_pair(cs[q], tv[own[q]]);
+          tk[own[q]] = -1;
+          tv[own[q]] = 0;
         }
       __syncthreads();
       continue;
@@ -1423,35 +1447,33 @@ __device__ __forceinline__ void role_hub_insert(const Dev& D, const HubIn& H, in
     // Flush in rounds: every pending slot of the thread tries its current
     // table slot (the compare-and-swaps of a round are in flight
     // together); hits add their weight, collisions probe on.
-    constexpr int F = 8;
-    for (int s0 = 0; s0 < kHubTS; s0 += F * kBlock) {
-      int32_t fk[F], fv[F];
-      uint32_t fp[F];
-      uint32_t pend = 0;
+    int32_t fv[kPer];
+    uint32_t fp[kPer];
+    uint32_t pend = 0;
 #pragma unroll
-      for (int q = 0; q < F; ++q) {
-        const int sl = s0 + threadIdx.x + q * kBlock;
-        fk[q] = tk[sl];
-        fv[q] = tv[sl];
-        fp[q] = fk[q] >= 0 ? hash_slot(static_cast<uint32_t>(fk[q]), tsz) : 0;
-        if (fk[q] >= 0) pend |= 1u << q;
-      }
-      while (pend) {
-        unsigned long long old[F];
+    for (int q = 0; q < kPer; ++q) {
+      fv[q] = own[q] >= 0 ? tv[own[q]] : 0;
+      fp[q] = own[q] >= 0 ? hash_slot(static_cast<uint32_t>(cs[q]), tsz) : 0;
+      if (own[q] < 0) continue;
+      pend |= 1u << q;
+      tk[own[q]] = -1;
+      tv[own[q]] = 0;
+    }
+    while (pend) {
+      unsigned long long old[kPer];
 #pragma unroll
-        for (int q = 0; q < F; ++q)
-          old[q] = (pend >> q) & 1u ? atomicCAS(&tab[fp[q]], kEmptyPair, pack_pair(fk[q], fv[q])) : kEmptyPair;
+      for (int q = 0; q < kPer; ++q)
+        old[q] = (pend >> q) & 1u ? atomicCAS(&tab[fp[q]], kEmptyPair, pack_pair(cs[q], fv[q])) : kEmptyPair;
 #pragma unroll
-        for (int q = 0; q < F; ++q) {
-          if (!((pend >> q) & 1u)) continue;
-          if (old[q] == kEmptyPair) {
-            pend &= ~(1u << q);
-          } else if (static_cast<int32_t>(old[q] >> 32) == fk[q]) {
-            atomicAdd(&tab[fp[q]], static_cast<unsigned long long>(static_cast<uint32_t>(fv[q])));
-            pend &= ~(1u << q);
-          } else {
-            fp[q] = fp[q] + 1 == tsz ? 0 : fp[q] + 1;
-          }
+      for (int q = 0; q < kPer; ++q) {
+        if (!((pend >> q) & 1u)) continue;
+        if (old[q] == kEmptyPair) {
+          pend &= ~(1u << q);
+        } else if (static_cast<int32_t>(old[q] >> 32) == cs[q]) {
+          atomicAdd(&tab[fp[q]], static_cast<unsigned long long>(static_cast<uint32_t>(fv[q])));
+          pend &= ~(1u << q);
+        } else {
+          fp[q] = fp[q] + 1 == tsz ? 0 : fp[q] + 1;
         }
       }
     }
@@ -1627,12 +1649,16 @@ __global__ void __launch_bounds__(kBlock) k_hub_decide(Dev D, const int32_t* __r
         __syncthreads();
         block_exscan(s_pre, nu, s_w);
         const int32_t total = s_pre[nu];
+        // a table of twice the segment's pairs (a few dozen on a converged
+        // hub), 4096 slots at most
+        int ts = kBlock;
+        while (ts < 2 * total && ts < kHubTS) ts <<= 1;
         for (uint32_t log2r = 0;; ++log2r) {
           bool redo = false;
           bg = LLONG_MIN;
           bc = INT_MAX;
           for (uint32_t r = 0; r < (1u << log2r) && !redo; ++r) {
-            for (int t = threadIdx.x; t < kHubTS; t += kBlock) {
+            for (int t = threadIdx.x; t < ts; t += kBlock) {
               t_key[t] = -1;
               t_val[t] = 0;
             }
@@ -1657,7 +1683,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_decide(Dev D, const int32_t* __r
                 s_ovf = 1;
                 continue;
               }
-              uint32_t p = hk & (kHubTS - 1);
+              uint32_t p = hk & (ts - 1);
               while (true) {
                 const int32_t old = atomicCAS(&t_key[p], -1, c);
                 if (old == -1 || old == c) {
@@ -1665,19 +1691,20 @@ __global__ void __launch_bounds__(kBlock) k_hub_decide(Dev D, const int32_t* __r
                   atomicAdd(&t_val[p], x);
                   break;
                 }
-                p = (p + 1) & (kHubTS - 1);
+                p = (p + 1) & (ts - 1);
               }
             }
             __syncthreads();
             if (s_ovf) {
               redo = true;
             } else {
-              for (int t0 = 0; t0 < kHubTS; t0 += kDecideSlots * kBlock) {
+              for (int t0 = 0; t0 < ts; t0 += kDecideSlots * kBlock) {
                 int32_t cc[kDecideSlots], vv[kDecideSlots];
 #pragma unroll
                 for (int q = 0; q < kDecideSlots; ++q) {
-                  cc[q] = t_key[t0 + threadIdx.x + q * kBlock];
-                  vv[q] = t_val[t0 + threadIdx.x + q * kBlock];
+                  const int t = t0 + threadIdx.x + q * kBlock;
+                  cc[q] = t < ts ? t_key[t] : -1;
+                  vv[q] = t < ts ? t_val[t] : 0;
                 }
                 best_of(D, two_m, kid, Ki, Sd, cc, vv, bg, bc);
               }
