@@ -980,7 +980,7 @@ lv_status many_graph(void* desc, size_t desc_bytes, int32_t count, const lv_para
   LV_HIP(hipStreamBeginCapture(G.cap, hipStreamCaptureModeThreadLocal));
   (void)hipMemcpyAsync(d, G.host, bytes, hipMemcpyHostToDevice, G.cap);
   launch_many_df(reinterpret_cast<const int32_t*>(d), reinterpret_cast<ManyItem*>(d + kManyHeader),
-                 std::min(bucket, tu.grid), p, tu.wave_max_degree, G.cap);
+                 std::min(bucket, tu.grid), p, tu.wave_max_degree, bucket <= kManyWideItems, G.cap);
   (void)hipMemcpyAsync(G.host, d, bytes, hipMemcpyDeviceToHost, G.cap);
   LV_HIP(hipStreamEndCapture(G.cap, &graph));
   hipGraphExec_t exec = nullptr;
@@ -1429,7 +1429,7 @@ lv_status lv_autotune_many(const lv_item* items, int32_t count, const lv_params*
   int32_t zero = 0;
   LV_HIP(hipMemcpyAsync(d, &zero, sizeof(int32_t), hipMemcpyHostToDevice, st));
   launch_many_df(reinterpret_cast<const int32_t*>(d), reinterpret_cast<ManyItem*>(d + kManyHeader), 1, *p,
-                 cand[0].wave_max_degree, st);
+                 cand[0].wave_max_degree, count <= kManyWideItems, st);
   LV_CHECK_LAUNCH();
   LV_HIP(hipStreamSynchronize(st));
   double best_t = 0.0;
@@ -1444,7 +1444,7 @@ lv_status lv_autotune_many(const lv_item* items, int32_t count, const lv_params*
     LV_HIP(hipMemcpyAsync(d + kManyHeader, grp.data(), sizeof(ManyItem) * grp.size(), hipMemcpyHostToDevice, st));
     LV_HIP(hipEventRecord(e0, st));
     launch_many_df(reinterpret_cast<const int32_t*>(d), reinterpret_cast<ManyItem*>(d + kManyHeader),
-                   std::min(gn, cand[c].grid), *p, cand[c].wave_max_degree, st);
+                   std::min(gn, cand[c].grid), *p, cand[c].wave_max_degree, count <= kManyWideItems, st);
     LV_CHECK_LAUNCH();
     LV_HIP(hipEventRecord(e1, st));
     LV_HIP(hipMemcpyAsync(grp.data(), d + kManyHeader, sizeof(ManyItem) * grp.size(), hipMemcpyDeviceToHost, st));

@@ -556,8 +556,10 @@ size_t many_scratch_bytes(int32_t n, int32_t max_updates);
 constexpr size_t kManyHeader = 256;
 // wave_deg: rows up to this many arcs take one wavefront (at most
 // kManyWaveDeg), longer ones the whole workgroup.
+// wide: workgroups of 1024 threads (else 256).
+constexpr int32_t kManyWideItems = 512;  // two per compute unit
 void launch_many_df(const int32_t* count, ManyItem* items, int32_t grid, const lv_params& p, int32_t wave_deg,
-                    hipStream_t st);
+                    bool wide, hipStream_t st);
 
 // move.hip
 struct MoveArgs {

@@ -287,7 +287,7 @@ class Edges:
 
     def cvals(self) -> tuple:
         """The lv_edges fields in order (null pointers as 0)."""
-        n = self.count
+        n = self.u.numel()
         if n == 0:
             return 0, 0, 0, 0
         return self.u.data_ptr(), self.v.data_ptr(), self.w.data_ptr(), n
@@ -615,7 +615,7 @@ def _many(fn, graphs, batches, states, scratches, max_updates, prm, ws, desc, st
     items = np.zeros(max(count, 1), dtype=_item_dtype())
     if count:
         # one record per item, fields in lv_item order
-        items[:count] = [g.cvals() + s.cvals() + b.dels.cvals() + b.ins.cvals() + (x.data_ptr(), cap)
+        items[:count] = [(*g.cvals(), *s.cvals(), *b.dels.cvals(), *b.ins.cvals(), x.data_ptr(), cap)
                          for g, s, b, x, cap in zip(graphs, states, batches, scratches, caps)]
     need = int(L.lv_many_desc_bytes(count))
     if desc is None or desc.numel() < need:
