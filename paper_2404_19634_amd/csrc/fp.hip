@@ -8,11 +8,12 @@
 //
 // Work mapping (wave64): rows up to 256 arcs take one wavefront with an LDS
 // table of 512 (community, FP64 weight) slots; rows up to 2048 arcs one
-// workgroup with a 4096-slot LDS table; longer rows one workgroup with a
-// table of 2 x deg slots in the workspace pool.  The frontier is a bitmask;
-// movers push their neighbours.  Aggregation gives each community one
-// workgroup, whose table (LDS, or pool slots past 2048 arcs of member
-// volume) sums the members' arcs by neighbouring community in FP64; the
+// workgroup with a 4096-slot LDS table; longer rows one wide workgroup with
+// an 8192-slot LDS table, or one of 2 x deg slots in the workspace pool where
+// a row's communities exceed that.  The frontier is a bitmask; movers push
+// their neighbours.  Aggregation gives each community one workgroup, whose
+// table (LDS, or pool slots for a large community of a level of many) sums
+// the members' arcs by neighbouring community in FP64; the
 // sums are stored as float32 weights of a slack CSR whose row capacities
 // are the member volumes.
 #include <cfloat>
@@ -80,31 +81,6 @@ __device__ __forceinline__ void wave_arg(double& g, int32_t& c) {
       c = oc;
     }
   }
-}
-__device__ __forceinline__ void block_arg(double& g, int32_t& c, double* sg, int32_t* sc) {
-  wave_arg(g, c);
-  __syncthreads();
-  if (lane_id() == 0) {
-    sg[threadIdx.x / kWave] = g;
-    sc[threadIdx.x / kWave] = c;
-  }
-  __syncthreads();
-  for (int k = 0; k < kFNW; ++k)
-    if (better_f(sg[k], sc[k], g, c)) {
-      g = sg[k];
-      c = sc[k];
-    }
-  __syncthreads();
-}
-__device__ __forceinline__ double block_sum_d(double v, double* s) {
-  v = wave_sum_d(v);
-  __syncthreads();
-  if (lane_id() == 0) s[threadIdx.x / kWave] = v;
-  __syncthreads();
-  double t = 0.0;
-  for (int k = 0; k < kFNW; ++k) t += s[k];
-  __syncthreads();
-  return t;
 }
 __device__ __forceinline__ bool weight_ok(float w) { return isfinite(w) && w > 0.0f; }
 
@@ -507,7 +483,7 @@ struct FMove {
   uint32_t* next;
   const int32_t* list[FB_N];
   int64_t cnt[FB_N];  // rows per bin (-1: in the counter block)
-  double m;  // 2m / 2
+  const double* two_m;
   int32_t guard;
   int64_t* ctr;
   int64_t pool_slots;
@@ -535,22 +511,28 @@ __device__ __forceinline__ bool commit(const FMove& M, int32_t i, int32_t d, int
   return true;
 }
 
-// LDS table insert: (c, x) into keys/vals of `size` slots (power of two)
-__device__ __forceinline__ void tab_add(int32_t* keys, double* vals, uint32_t size, int32_t c, double x) {
+// Table insert: (c, x) into keys/vals of `size` slots (power of two); returns
+// whether c was new.
+__device__ __forceinline__ bool tab_add(int32_t* keys, double* vals, uint32_t size, int32_t c, double x) {
   uint32_t h = hash_slot(static_cast<uint32_t>(c), size);
   while (true) {
     const int32_t old = atomicCAS(&keys[h], -1, c);
     if (old == -1 || old == c) {
       atomicAdd(&vals[h], x);
-      return;
+      return old == -1;
     }
     h = (h + 1) & (size - 1);
   }
 }
 
+// Every scan does nothing once the error slot is set (a membership outside
+// [0, n), or a batch that names a vertex outside it).
 __global__ void __launch_bounds__(kBlock) k_f_scan_wave(FMove M) {
   __shared__ int32_t s_keys[kFNW][kFWaveSlots];
   __shared__ double s_vals[kFNW][kFWaveSlots];
+  constexpr int U = kFWaveMax / kWave;
+  if (M.ctr[F_ERR]) return;
+  const double m = *M.two_m / 2.0;
   const int lane = lane_id();
   const int wv = threadIdx.x / kWave;
   int32_t* keys = s_keys[wv];
@@ -559,6 +541,14 @@ __global__ void __launch_bounds__(kBlock) k_f_scan_wave(FMove M) {
   const int64_t nw = static_cast<int64_t>(gridDim.x) * kFNW;
   int64_t movers = 0, expand = 0;
   double dq_sum = 0.0;
+  // (a lane owns the slots it inserts: it reads their sums and clears them)
+  for (int t = lane; t < kFWaveSlots; t += kWave) {
+    keys[t] = -1;
+    vals[t] = 0.0;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   for (int64_t idx = blockIdx.x * static_cast<int64_t>(kFNW) + wv; idx < count; idx += nw) {
     const int32_t i = M.list[FB_WAVE][idx];
     const int64_t s = M.g.row_start[i];
@@ -566,38 +556,63 @@ __global__ void __launch_bounds__(kBlock) k_f_scan_wave(FMove M) {
     const int32_t d = M.C[i];
     const double Ki = M.K[i];
     const uint32_t ts = max(64u, 1u << (32 - __clz(static_cast<uint32_t>(2 * max(deg, 1) - 1))));
-    for (uint32_t t = lane; t < ts; t += kWave) {
-      keys[t] = -1;
-      vals[t] = 0.0;
+    const int nu = __builtin_amdgcn_readfirstlane((deg + kWave - 1) / kWave);  // steps that hold arcs
+    int32_t js[U], cs[U], own[U];
+    float xs[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (q >= nu) continue;
+      const int32_t k = lane + q * kWave;
+      js[q] = k < deg ? M.g.col[s + k] : i;
+      xs[q] = k < deg ? M.g.w[s + k] : 0.0f;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const double Sd = M.Sigma[d];
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (q < nu) cs[q] = js[q] != i ? M.C[js[q]] : d;
     double kid = 0.0;
-    for (int32_t k = lane; k < deg; k += kWave) {
-      const int32_t j = M.g.col[s + k];
-      if (j == i) continue;
-      const double x = static_cast<double>(M.g.w[s + k]);
-      const int32_t c = M.C[j];
-      if (c == d)
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      own[q] = -1;
+      if (q >= nu || js[q] == i) continue;
+      const double x = static_cast<double>(xs[q]);
+      if (cs[q] == d) {
         kid += x;
-      else
-        tab_add(keys, vals, ts, c, x);
+        continue;
+      }
+      uint32_t h = hash_slot(static_cast<uint32_t>(cs[q]), ts);
+      while (true) {
+        const int32_t old = atomicCAS(&keys[h], -1, cs[q]);
+        if (old == -1 || old == cs[q]) {
+          atomicAdd(&vals[h], x);
+          if (old == -1) own[q] = static_cast<int32_t>(h);
+          break;
+        }
+        h = (h + 1) & (ts - 1);
+      }
     }
     kid = wave_sum_d(kid);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const double Sd = M.Sigma[d];
     double bg = -DBL_MAX;
     int32_t bc = INT_MAX;
-    for (uint32_t t = lane; t < ts; t += kWave) {
-      const int32_t c = keys[t];
-      if (c < 0) continue;
-      const double g = dq_of(M.m, vals[t], kid, Ki, M.Sigma[c], Sd);
-      if (better_f(g, c, bg, bc)) {
+    double vv[U], sg[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (q >= nu) continue;
+      vv[q] = own[q] >= 0 ? vals[own[q]] : 0.0;
+      sg[q] = own[q] >= 0 ? M.Sigma[cs[q]] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (q >= nu || own[q] < 0) continue;
+      keys[own[q]] = -1;
+      vals[own[q]] = 0.0;
+      const double g = dq_of(m, vv[q], kid, Ki, sg[q], Sd);
+      if (better_f(g, cs[q], bg, bc)) {
         bg = g;
-        bc = c;
+        bc = cs[q];
       }
     }
     wave_arg(bg, bc);
@@ -626,16 +641,108 @@ __global__ void __launch_bounds__(kBlock) k_f_scan_wave(FMove M) {
   }
 }
 
-// rows past the wavefront bin: one workgroup each; the table lies in LDS
-// (up to 2048 arcs) or in pool slots (2 x deg, reserved per row)
+// Rows past the wavefront bin: one workgroup each.  Up to 2048 arcs 256
+// threads and a 4096-slot LDS table.  Longer (hub) rows 1024 threads and 8192
+// slots, which hold the neighbour communities of any row that does not have
+// over 6144 of them; one that does takes 2 x deg pool slots.
+// (256 threads with the pool's table for every hub row: 51 us a launch over a
+// few rows of up to 5000 arcs of a 250,001-vertex power-law graph, a chain of
+// 20 arcs per thread and every insert an L2 atomic; this: 12.7 us.)
+constexpr int kFWide = 1024;               // threads of the wide workgroups
+constexpr int kFWideSlots = 8192;
+constexpr int kFWideKeys = kFWideSlots - 2 * kFWide;  // (room for the inserts in flight)
+
+struct FBest {
+  double kid, g;
+  int32_t c;
+};
+// The best move of row [s, s + deg) of vertex i (community d) by the
+// workgroup's NT threads with the table keys/vals of ts slots.  LIMIT: gives
+// up, with *over set, where the row has kFWideKeys communities.
+template <int NT, bool GLOBAL, bool LIMIT>
+__device__ __forceinline__ FBest group_best(const FMove& M, double m, int32_t i, int64_t s, int32_t deg, int32_t d,
+                                            double Ki, int32_t* keys, double* vals, uint32_t ts, int32_t* s_n,
+                                            int32_t* over, double* s_g, int32_t* s_c) {
+  constexpr int NW = NT / kWave;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  for (uint32_t t = threadIdx.x; t < ts; t += NT) {
+    keys[t] = -1;
+    vals[t] = 0.0;
+  }
+  if (LIMIT && threadIdx.x == 0) *s_n = *over = 0;
+  __syncthreads();
+  double kid = 0.0;
+  for (int32_t k0 = threadIdx.x; k0 < deg; k0 += 4 * NT) {  // four arcs of a thread in flight
+    int32_t js[4], cs[4];
+    float xs[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const bool in = k0 + q * NT < deg;
+      js[q] = in ? M.g.col[s + k0 + q * NT] : i;
+      xs[q] = in ? M.g.w[s + k0 + q * NT] : 0.0f;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cs[q] = js[q] != i ? M.C[js[q]] : d;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (js[q] == i) continue;
+      const double x = static_cast<double>(xs[q]);
+      if (cs[q] == d) {
+        kid += x;
+        continue;
+      }
+      if (LIMIT && __hip_atomic_load(s_n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) >= kFWideKeys) {
+        *over = 1;
+        continue;
+      }
+      const bool fresh = tab_add(keys, vals, ts, cs[q], x);
+      if (LIMIT && fresh) atomicAdd(s_n, 1);
+    }
+  }
+  kid = wave_sum_d(kid);
+  if (lane == 0) s_g[wv] = kid;
+  __syncthreads();
+  FBest r{0.0, -DBL_MAX, INT_MAX};
+  if (LIMIT && *over) return r;  // (uniform)
+  for (int q = 0; q < NW; ++q) r.kid += s_g[q];
+  const double Sd = M.Sigma[d];
+  for (uint32_t t = threadIdx.x; t < ts; t += NT) {
+    const int32_t c = GLOBAL ? ld_agent(&keys[t]) : keys[t];
+    if (c < 0) continue;
+    const double x = GLOBAL ? ld_agent(&vals[t]) : vals[t];
+    const double g = dq_of(m, x, r.kid, Ki, M.Sigma[c], Sd);
+    if (better_f(g, c, r.g, r.c)) {
+      r.g = g;
+      r.c = c;
+    }
+  }
+  wave_arg(r.g, r.c);
+  __syncthreads();
+  if (lane == 0) {
+    s_g[wv] = r.g;
+    s_c[wv] = r.c;
+  }
+  __syncthreads();
+  for (int q = 0; q < NW; ++q)
+    if (better_f(s_g[q], s_c[q], r.g, r.c)) {
+      r.g = s_g[q];
+      r.c = s_c[q];
+    }
+  return r;
+}
+
 template <bool HUB>
-__global__ void __launch_bounds__(kBlock) k_f_scan_group(FMove M) {
-  __shared__ int32_t s_keys[HUB ? 1 : kFBlockSlots];
-  __shared__ double s_vals[HUB ? 1 : kFBlockSlots];
-  __shared__ double s_g[kFNW];
-  __shared__ int32_t s_c[kFNW];
+__global__ void __launch_bounds__(HUB ? kFWide : kBlock) k_f_scan_group(FMove M) {
+  constexpr int NT = HUB ? kFWide : kBlock;
+  constexpr int kSlots = HUB ? kFWideSlots : kFBlockSlots;
+  __shared__ int32_t s_keys[kSlots];
+  __shared__ double s_vals[kSlots];
+  __shared__ double s_g[NT / kWave];
+  __shared__ int32_t s_c[NT / kWave];
   __shared__ int64_t s_off;
-  __shared__ int32_t s_mv;
+  __shared__ int32_t s_mv, s_n, s_over;
+  if (M.ctr[F_ERR]) return;
+  const double m = *M.two_m / 2.0;
   const int b = HUB ? FB_HUB : FB_BLOCK;
   const int64_t count = rows_in(M, b);
   int64_t movers = 0, expand = 0;
@@ -646,10 +753,10 @@ __global__ void __launch_bounds__(kBlock) k_f_scan_group(FMove M) {
     const int32_t deg = M.g.row_len[i];
     const int32_t d = M.C[i];
     const double Ki = M.K[i];
-    int32_t* keys;
-    double* vals;
-    uint32_t ts;
-    if (HUB) {
+    uint32_t ts = 64u;
+    while (ts < static_cast<uint32_t>(kSlots) && ts < 2u * static_cast<uint32_t>(deg)) ts <<= 1;
+    FBest r = group_best<NT, false, HUB>(M, m, i, s, deg, d, Ki, s_keys, s_vals, ts, &s_n, &s_over, s_g, s_c);
+    if (HUB && s_over) {
       ts = 1u << (32 - __clz(static_cast<uint32_t>(2 * deg - 1)));
       if (threadIdx.x == 0) {
         const int64_t off = static_cast<int64_t>(atomicAdd(reinterpret_cast<unsigned long long*>(&M.ctr[F_POOL]),
@@ -658,54 +765,19 @@ __global__ void __launch_bounds__(kBlock) k_f_scan_group(FMove M) {
         if (s_off < 0) flag(M.ctr, LV_EWORKSPACE);
       }
       __syncthreads();
-      if (s_off < 0) break;  // (uniform) the error is flagged
-      keys = M.pkeys + s_off;
-      vals = M.pvals + s_off;
-    } else {
-      ts = kFBlockSlots;
-      keys = s_keys;
-      vals = s_vals;
+      if (s_off < 0) return;  // (uniform) the error is flagged
+      r = group_best<NT, true, false>(M, m, i, s, deg, d, Ki, M.pkeys + s_off, M.pvals + s_off, ts, nullptr, nullptr,
+                                      s_g, s_c);
     }
-    for (uint32_t t = threadIdx.x; t < ts; t += kBlock) {
-      keys[t] = -1;
-      vals[t] = 0.0;
-    }
-    __syncthreads();
-    double kid = 0.0;
-    for (int32_t k = threadIdx.x; k < deg; k += kBlock) {
-      const int32_t j = M.g.col[s + k];
-      if (j == i) continue;
-      const double x = static_cast<double>(M.g.w[s + k]);
-      const int32_t c = M.C[j];
-      if (c == d)
-        kid += x;
-      else
-        tab_add(keys, vals, ts, c, x);
-    }
-    kid = block_sum_d(kid, s_g);
-    const double Sd = M.Sigma[d];
-    double bg = -DBL_MAX;
-    int32_t bc = INT_MAX;
-    for (uint32_t t = threadIdx.x; t < ts; t += kBlock) {
-      const int32_t c = HUB ? ld_agent(&keys[t]) : keys[t];
-      if (c < 0) continue;
-      const double x = HUB ? ld_agent(&vals[t]) : vals[t];
-      const double g = dq_of(M.m, x, kid, Ki, M.Sigma[c], Sd);
-      if (better_f(g, c, bg, bc)) {
-        bg = g;
-        bc = c;
-      }
-    }
-    block_arg(bg, bc, s_g, s_c);
-    if (threadIdx.x == 0) s_mv = commit(M, i, d, bc, bg, Ki) ? 1 : 0;
+    if (threadIdx.x == 0) s_mv = commit(M, i, d, r.c, r.g, Ki) ? 1 : 0;
     __syncthreads();
     if (s_mv) {
       if (threadIdx.x == 0) {
         movers += 1;
         expand += deg;
-        dq_sum += bg;
+        dq_sum += r.g;
       }
-      for (int32_t k = threadIdx.x; k < deg; k += kBlock) {
+      for (int32_t k = threadIdx.x; k < deg; k += NT) {
         const int32_t j = M.g.col[s + k];
         if (j != i) set_bit(M.next, j);
       }
@@ -818,67 +890,212 @@ __global__ void k_f_set_all(uint32_t* __restrict__ bm, int32_t n, int64_t words)
 // ---------------------------------------------------------------------------
 // Aggregation (Alg. 6)
 // ---------------------------------------------------------------------------
+// The row of super-vertex c by the workgroup's NT threads: a wavefront takes
+// a member at a time, its arcs in lanes, the next member's row looked up
+// meanwhile; arcs inside the community (its most frequent key) are summed in
+// registers.  keys/vals: ts slots, ts >= 2 x the keys there can be.
+template <int NT, bool GLOBAL>
+__device__ __forceinline__ void aggregate_one(const FG& g, const int32_t* __restrict__ C,
+                                              const int32_t* __restrict__ coff, const int32_t* __restrict__ cmem,
+                                              int32_t c, int64_t v0, int32_t* __restrict__ out_len,
+                                              int32_t* __restrict__ out_col, float* __restrict__ out_w,
+                                              double* __restrict__ K2, double* __restrict__ S2, int32_t* keys,
+                                              double* vals, uint32_t ts, double* s_r, int32_t* s_n) {
+  constexpr int NW = NT / kWave;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
+  for (uint32_t t = threadIdx.x; t < ts; t += NT) {
+    keys[t] = -1;
+    vals[t] = 0.0;
+  }
+  if (threadIdx.x == 0) *s_n = 0;
+  __syncthreads();
+  const int32_t m1 = coff[c + 1];
+  int32_t q = coff[c] + wv;
+  int64_t s = 0;
+  int32_t len = 0;
+  if (q < m1) {
+    const int32_t i = cmem[q];
+    s = g.row_start[i];
+    len = g.row_len[i];
+  }
+  double self = 0.0;
+  bool any = false;
+  while (q < m1) {
+    const int32_t nq = q + NW;
+    int64_t ns = 0;
+    int32_t nl = 0;
+    if (nq < m1) {
+      const int32_t i = cmem[nq];
+      ns = g.row_start[i];
+      nl = g.row_len[i];
+    }
+    for (int32_t k = lane; k < len; k += kWave) {
+      const int32_t e = C[g.col[s + k]];
+      const double x = static_cast<double>(g.w[s + k]);
+      if (e == c) {
+        self += x;
+        any = true;
+      } else {
+        tab_add(keys, vals, ts, e, x);
+      }
+    }
+    q = nq;
+    s = ns;
+    len = nl;
+  }
+  self = wave_sum_d(self);
+  if (__any(any) && lane == 0) tab_add(keys, vals, ts, c, self);
+  __syncthreads();
+  double k2 = 0.0;
+  for (uint32_t t = threadIdx.x; t < ts; t += NT) {
+    const int32_t e = GLOBAL ? ld_agent(&keys[t]) : keys[t];
+    if (e < 0) continue;
+    const float x = static_cast<float>(GLOBAL ? ld_agent(&vals[t]) : vals[t]);
+    const int32_t p = atomicAdd(s_n, 1);
+    out_col[v0 + p] = e;
+    out_w[v0 + p] = x;
+    k2 += static_cast<double>(x);
+  }
+  k2 = wave_sum_d(k2);
+  if (lane == 0) s_r[wv] = k2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double t = 0.0;
+    for (int k = 0; k < NW; ++k) t += s_r[k];
+    out_len[c] = *s_n;
+    K2[c] = t;
+    S2[c] = t;
+  }
+  __syncthreads();
+}
+
 // One workgroup per community c: its members' arcs summed by neighbouring
 // community (self-loops included) in FP64, written as the float32 row of
-// super-vertex c at vstart[c] (capacity: the members' volume).
-__global__ void __launch_bounds__(kBlock) k_f_aggregate(FG g, const int32_t* __restrict__ C,
-                                                      const int32_t* __restrict__ coff,
-                                                      const int32_t* __restrict__ cmem,
-                                                      const int64_t* __restrict__ vstart, int32_t nc,
-                                                      int32_t* __restrict__ out_len, int32_t* __restrict__ out_col,
-                                                      float* __restrict__ out_w, double* __restrict__ K2,
-                                                      double* __restrict__ S2, int32_t* __restrict__ pkeys,
-                                                      double* __restrict__ pvals) {
+// super-vertex c at vstart[c] (capacity: the members' volume).  Communities
+// of up to 2048 arcs take 256 threads and an LDS table of twice their volume;
+// larger ones, which a workgroup finds among the communities of its residue
+// class, 1024 threads and an LDS table where twice the level's communities fit
+// it, else pool slots.
+// (256 threads walking one member after another, 28 arcs at a time, and the
+// pool's table past 2048 arcs: 986 us for 104 communities of 14,000 arcs;
+// this: 45 us, the members' chains of dependent loads.)
+struct FAgg {
+  FG g;
+  const int32_t *C, *coff, *cmem;
+  const int64_t* vstart;
+  int32_t nc;
+  int32_t *out_len, *out_col;
+  float* out_w;
+  double *K2, *S2;
+  int32_t* pkeys;
+  double* pvals;
+};
+__device__ __forceinline__ uint32_t agg_slots(int64_t vol, int32_t nc) {
+  const int64_t keys = min(vol, static_cast<int64_t>(nc));
+  uint32_t ts = 64u;
+  while (ts < 2 * keys) ts <<= 1;
+  return ts;
+}
+__global__ void __launch_bounds__(kBlock) k_f_aggregate(FAgg A) {
   __shared__ int32_t s_keys[kFBlockSlots];
   __shared__ double s_vals[kFBlockSlots];
   __shared__ double s_r[kFNW];
   __shared__ int32_t s_n;
-  for (int64_t c = blockIdx.x; c < nc; c += gridDim.x) {
-    const int64_t v0 = vstart[c], vol = vstart[c + 1] - v0;
-    const bool big = vol > kFBlockMax;
-    const uint32_t ts = big ? static_cast<uint32_t>(1) << (32 - __clz(static_cast<uint32_t>(2 * vol - 1)))
-                            : static_cast<uint32_t>(kFBlockSlots);
-    int32_t* keys = big ? pkeys + 4 * v0 : s_keys;  // ts <= 4 vol
-    double* vals = big ? pvals + 4 * v0 : s_vals;
-    for (uint32_t t = threadIdx.x; t < ts; t += kBlock) {
-      keys[t] = -1;
-      vals[t] = 0.0;
-    }
-    if (threadIdx.x == 0) s_n = 0;
+  for (int64_t c = blockIdx.x; c < A.nc; c += gridDim.x) {
+    const int64_t v0 = A.vstart[c], vol = A.vstart[c + 1] - v0;
+    if (vol > kFBlockMax) continue;
+    aggregate_one<kBlock, false>(A.g, A.C, A.coff, A.cmem, static_cast<int32_t>(c), v0, A.out_len, A.out_col, A.out_w,
+                                 A.K2, A.S2, s_keys, s_vals, agg_slots(vol, A.nc), s_r, &s_n);
+  }
+}
+__global__ void __launch_bounds__(kFWide) k_f_aggregate_big(FAgg A) {
+  __shared__ int32_t s_keys[kFWideSlots];
+  __shared__ double s_vals[kFWideSlots];
+  __shared__ double s_r[kFWide / kWave];
+  __shared__ int32_t s_list[kFWide];
+  __shared__ int32_t s_n, s_m;
+  for (int64_t k0 = 0; k0 * gridDim.x + blockIdx.x < A.nc; k0 += kFWide) {
+    if (threadIdx.x == 0) s_m = 0;
     __syncthreads();
-    for (int32_t q = coff[c]; q < coff[c + 1]; ++q) {
-      const int32_t i = cmem[q];
-      const int64_t s = g.row_start[i];
-      const int32_t len = g.row_len[i];
-      for (int32_t k = threadIdx.x; k < len; k += kBlock)
-        tab_add(keys, vals, ts, C[g.col[s + k]], static_cast<double>(g.w[s + k]));
-    }
+    const int64_t mine = (k0 + threadIdx.x) * gridDim.x + blockIdx.x;
+    if (mine < A.nc && A.vstart[mine + 1] - A.vstart[mine] > kFBlockMax)
+      s_list[atomicAdd(&s_m, 1)] = static_cast<int32_t>(mine);
     __syncthreads();
-    double k2 = 0.0;
-    for (uint32_t t = threadIdx.x; t < ts; t += kBlock) {
-      const int32_t d = big ? ld_agent(&keys[t]) : keys[t];
-      if (d < 0) continue;
-      const float x = static_cast<float>(big ? ld_agent(&vals[t]) : vals[t]);
-      const int32_t p = atomicAdd(&s_n, 1);
-      out_col[v0 + p] = d;
-      out_w[v0 + p] = x;
-      k2 += static_cast<double>(x);
-    }
-    k2 = block_sum_d(k2, s_r);
-    if (threadIdx.x == 0) {
-      out_len[c] = s_n;
-      K2[c] = k2;
-      S2[c] = k2;
+    const int32_t found = s_m;
+    for (int32_t q = 0; q < found; ++q) {
+      const int32_t c = s_list[q];
+      const int64_t v0 = A.vstart[c], vol = A.vstart[c + 1] - v0;
+      const uint32_t ts = agg_slots(vol, A.nc);
+      if (ts <= static_cast<uint32_t>(kFWideSlots))
+        aggregate_one<kFWide, false>(A.g, A.C, A.coff, A.cmem, c, v0, A.out_len, A.out_col, A.out_w, A.K2, A.S2,
+                                     s_keys, s_vals, ts, s_r, &s_n);
+      else  // (ts <= 4 vol)
+        aggregate_one<kFWide, true>(A.g, A.C, A.coff, A.cmem, c, v0, A.out_len, A.out_col, A.out_w, A.K2, A.S2,
+                                    A.pkeys + 4 * v0, A.pvals + 4 * v0, ts, s_r, &s_n);
     }
     __syncthreads();
   }
 }
 
-__global__ void k_f_sigma(const int32_t* __restrict__ C, const double* __restrict__ K, int32_t n,
-                          double* __restrict__ Sigma) {
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    if (K[i] != 0.0) atomicAdd(&Sigma[C[i]], K[i]);
+// Sigma[C_i] += K_i, summed in LDS first (few communities take most of the
+// vertices, and device atomics on one address queue).
+constexpr int kFSumSlots = 2048;
+__global__ void __launch_bounds__(kFWide) k_f_sigma(const int32_t* __restrict__ C, const double* __restrict__ K,
+                                                        int32_t n, double* __restrict__ Sigma) {
+  __shared__ int32_t s_keys[kFSumSlots];
+  __shared__ double s_vals[kFSumSlots];
+  for (int t = threadIdx.x; t < kFSumSlots; t += kFWide) {
+    s_keys[t] = -1;
+    s_vals[t] = 0.0;
+  }
+  __syncthreads();
+  for (int64_t i = blockIdx.x * static_cast<int64_t>(kFWide) + threadIdx.x; i < n;
+       i += static_cast<int64_t>(gridDim.x) * kFWide) {
+    const int32_t c = C[i];
+    const double x = K[i];
+    if (x == 0.0) continue;
+    uint32_t h = hash_slot(static_cast<uint32_t>(c), kFSumSlots);
+    bool done = false;
+    for (int p = 0; p < 8 && !done; ++p) {
+      const int32_t old = atomicCAS(&s_keys[h], -1, c);
+      done = old == -1 || old == c;
+      if (done) atomicAdd(&s_vals[h], x);
+      h = (h + 1) & (kFSumSlots - 1);
+    }
+    if (!done) atomicAdd(&Sigma[c], x);
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < kFSumSlots; t += kFWide)
+    if (s_keys[t] >= 0 && s_vals[t] != 0.0) atomicAdd(&Sigma[s_keys[t]], s_vals[t]);
+}
+
+// The error slot, 2m and the statistics summed over their replicas, to
+// pinned host memory: one kernel and a wait (a copy of the counters to
+// pageable memory: 5 KB, staged).
+struct FRead {
+  int64_t err, movers, arcs, processed, expand, affected;
+  double dq, sum, sum2, two_m;
+};
+static_assert(FS_DQ == 5 && FS_SUM == 6 && FS_SUM2 == 7, "FRead lists the statistics in their order");
+__global__ void __launch_bounds__(kBlock) k_f_publish(const int64_t* __restrict__ ctr,
+                                                    const double* __restrict__ two_m, FRead* __restrict__ out) {
+  static_assert(kFReps * 8 == kBlock, "a thread per replica and statistic");
+  __shared__ int64_t s_v[kFReps * 8];
+  s_v[threadIdx.x] = ctr[F_STATS + (threadIdx.x / 8) * kCtrLine + threadIdx.x % 8];
+  __syncthreads();
+  const int k = threadIdx.x;
+  if (k < FS_DQ) {
+    int64_t v = 0;
+    for (int r = 0; r < kFReps; ++r) v += s_v[r * 8 + k];
+    (&out->movers)[k] = v;
+  } else if (k <= FS_SUM2) {
+    double v = 0.0;
+    for (int r = 0; r < kFReps; ++r) v += __longlong_as_double(s_v[r * 8 + k]);
+    (&out->dq)[k - FS_DQ] = v;
+  } else if (k == FS_SUM2 + 1) {
+    out->err = ctr[F_ERR];
+    out->two_m = *two_m;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -909,6 +1126,7 @@ struct FWs {
   int32_t *dpos = nullptr, *imode = nullptr;
   Workspace scan;  // scan partials only
   int64_t* ctr = nullptr;
+  const double* two_m = nullptr;  // the graph's
   size_t bytes = 0;
 };
 
@@ -1000,35 +1218,18 @@ lv_status setup(FWs& w, const lv_graph_f* g, void* ws, size_t ws_bytes) {
   if (!ws) return lv_fail(LV_EINVAL, "workspace pointer is null");
   if (ws_bytes < carve_f(w, nullptr, g->n, g->cap)) return lv_fail(LV_EWORKSPACE, "workspace too small");
   carve_f(w, ws, g->n, g->cap);
+  w.two_m = g->two_m;
   return LV_OK;
 }
 
-// Counters back on the host (the error slot and the statistics replicas).
-struct FRead {
-  int64_t err = 0, movers = 0, arcs = 0, processed = 0, expand = 0, affected = 0;
-  double dq = 0.0, sum = 0.0, sum2 = 0.0;
-};
+// The error slot, 2m and the statistics, on the host.
 lv_status read(const FWs& w, FRead& r, hipStream_t st) {
-  std::vector<int64_t> h(F_COUNT);
-  F_HIP(hipMemcpyAsync(h.data(), w.ctr, sizeof(int64_t) * F_COUNT, hipMemcpyDeviceToHost, st));
+  int64_t* host;
+  if (lv_status s = lv_pinned_host(&host)) return s;
+  hipLaunchKernelGGL(k_f_publish, dim3(1), dim3(kBlock), 0, st, w.ctr, w.two_m, reinterpret_cast<FRead*>(host));
+  F_HIP(hipGetLastError());
   F_HIP(hipStreamSynchronize(st));
-  r = FRead{};
-  r.err = h[F_ERR];
-  for (int k = 0; k < kFReps; ++k) {
-    const int64_t* x = h.data() + F_STATS + k * kCtrLine;
-    r.movers += x[FS_MOVERS];
-    r.arcs += x[FS_ARCS];
-    r.processed += x[FS_PROCESSED];
-    r.expand += x[FS_EXPAND];
-    r.affected += x[FS_AFFECTED];
-    double d;
-    std::memcpy(&d, x + FS_DQ, 8);
-    r.dq += d;
-    std::memcpy(&d, x + FS_SUM, 8);
-    r.sum += d;
-    std::memcpy(&d, x + FS_SUM2, 8);
-    r.sum2 += d;
-  }
+  std::memcpy(&r, host, sizeof(FRead));
   return LV_OK;
 }
 
@@ -1106,10 +1307,10 @@ bool edges_ok_f(const lv_edges_f* e) { return !e || e->count == 0 || (e->count >
 // at most that many rows each.
 void launch_scans_f(const FMove& M, uint32_t mask, int64_t hubs, int64_t big, int64_t rows, hipStream_t st) {
   if (mask & (1u << FB_HUB))
-    hipLaunchKernelGGL(k_f_scan_group<true>, dim3(static_cast<int>(std::min<int64_t>(hubs, 1024))), dim3(kBlock), 0,
+    hipLaunchKernelGGL(k_f_scan_group<true>, dim3(static_cast<int>(std::min<int64_t>(hubs, 256))), dim3(kFWide), 0,
                        st, M);
   if (mask & (1u << FB_BLOCK))
-    hipLaunchKernelGGL(k_f_scan_group<false>, dim3(static_cast<int>(std::min<int64_t>(big, 2048))), dim3(kBlock), 0,
+    hipLaunchKernelGGL(k_f_scan_group<false>, dim3(static_cast<int>(std::min<int64_t>(big, 768))), dim3(kBlock), 0,
                        st, M);
   if (mask & (1u << FB_WAVE))
     hipLaunchKernelGGL(k_f_scan_wave, dim3(blocks(rows * kWave, 4096)), dim3(kBlock), 0, st, M);
@@ -1119,7 +1320,7 @@ void launch_scans_f(const FMove& M, uint32_t mask, int64_t hubs, int64_t big, in
 // The plan's bins up to the wavefront's lie next to each other in a
 // sub-round's list and are one launch here.  (Binning per sub-round and
 // launching every bin: 17.4-22 ms for a static run on a 50,003-vertex SBM
-// graph, 4900 launches; planned: 4.4 ms.)
+// graph, 4900 launches; planned: 3.4-4.4 ms.)
 lv_status planned_rounds_f(FMove& M, const FWs& w, uint32_t* cur, uint32_t* ever, const std::vector<SubRound>& plan,
                            const lv_tuning& tu, lv_stats& S, hipStream_t st) {
   const PlanKeys pk = lv_plan_keys(plan, tu);
@@ -1133,11 +1334,12 @@ lv_status planned_rounds_f(FMove& M, const FWs& w, uint32_t* cur, uint32_t* ever
   a.mem = w.pkeys;  // (read back before the first scan uses the pool)
   TimerPair none;
   launch_plan(a, pk, &none, &none, st);
-  std::vector<int64_t> host((kPlanArcs + 8 * kPlanKeys) / 8);
-  F_HIP(hipMemcpyAsync(host.data(), w.pkeys, kPlanArcs + 8 * kPlanKeys, hipMemcpyDeviceToHost, st));
+  int64_t* host;
+  if (lv_status s = lv_pinned_host(&host)) return s;
+  F_HIP(hipMemcpyAsync(host, w.pkeys, kPlanArcs + 8 * kPlanKeys, hipMemcpyDeviceToHost, st));
   F_HIP(hipStreamSynchronize(st));
-  const int32_t* h = reinterpret_cast<const int32_t*>(host.data());
-  const int64_t* arcs = host.data() + kPlanArcs / 8;
+  const int32_t* h = reinterpret_cast<const int32_t*>(host);
+  const int64_t* arcs = host + kPlanArcs / 8;
   if (ever) S.vertices_affected += h[kPlanHost - kPlanTail + PT_AFFECTED];
   std::vector<int32_t> first(kPlanKeys);
   int32_t run = 0;
@@ -1204,12 +1406,7 @@ lv_status run_f(bool df, const lv_graph_f* g, const lv_edges_f* del, const lv_ed
                          state->Sigma, w.fa, w.ctr);
   }
   F_HIP(hipGetLastError());
-  double two_m = 0.0;
-  F_HIP(hipMemcpyAsync(&two_m, g->two_m, sizeof(double), hipMemcpyDeviceToHost, st));
-  FRead rd;
-  if ((s = read(w, rd, st))) return s;
-  if (rd.err) return dev_error(rd.err);
-  const double m = two_m / 2.0;
+  FRead rd{};
 
   FG L = L0;
   int32_t* Cl = state->C;
@@ -1225,15 +1422,14 @@ lv_status run_f(bool df, const lv_graph_f* g, const lv_edges_f* del, const lv_ed
     int64_t est = L.n;
     if (pass == 0 && df) est = 2 * (fbatch(del, ins).nd + fbatch(del, ins).ni);
     for (int32_t it = 0; it < p->max_iterations; ++it) {
-      if ((s = zero_stats(w, st))) return s;
+      if (pass + it > 0 && (s = zero_stats(w, st))) return s;  // (k_f_begin cleared them)
       const std::vector<SubRound> plan = lv_sub_rounds(LV_ASYNC, pass, est, L.n, tu);
-      FMove M{L, Cl, Kl, Sl, size, next, {w.list[FB_WAVE], w.list[FB_BLOCK], w.list[FB_HUB]}, {-1, -1, -1}, m,
+      FMove M{L, Cl, Kl, Sl, size, next, {w.list[FB_WAVE], w.list[FB_BLOCK], w.list[FB_HUB]}, {-1, -1, -1}, w.two_m,
               p->swap_guard, w.ctr, w.pool_slots, w.pkeys, w.pvals};
       if (plan.size() > 1) {
         if ((s = planned_rounds_f(M, w, cur, pass == 0 ? w.ever : nullptr, plan, tu, S, st))) return s;
       } else {
         const SubRound& r = plan[0];
-        F_HIP(hipMemsetAsync(w.ctr + F_LIST0, 0, sizeof(int64_t) * 4 * kCtrLine, st));  // lists and pool
         hipLaunchKernelGGL(k_f_bin, dim3(blocks(w.words, 4096)), dim3(kBlock), 0, st, cur,
                            pass == 0 ? w.ever : nullptr, L.row_len, L.n, r.hash_round, r.hash_shift, r.id_lo, r.id_hi,
                            r.deg_lo, r.deg_hi, 1, w.list[FB_WAVE], w.list[FB_BLOCK], w.list[FB_HUB], w.ctr);
@@ -1277,9 +1473,9 @@ lv_status run_f(bool df, const lv_graph_f* g, const lv_edges_f* del, const lv_ed
     launch_fill_members(Cl, L.n, w.coff, w.flags, w.cmem, st);
     const int k = pass & 1;
     exclusive_scan_i64(w.vol, w.lrs[k], nc, w.scan, st);
-    hipLaunchKernelGGL(k_f_aggregate, dim3(static_cast<int>(std::min<int32_t>(nc, 8192))), dim3(kBlock), 0, st, L,
-                       Cl, w.coff, w.cmem, w.lrs[k], nc, w.llen[k], w.lcol[k], w.lw[k], w.lK, w.lS, w.pkeys,
-                       w.pvals);
+    const FAgg A{L, Cl, w.coff, w.cmem, w.lrs[k], nc, w.llen[k], w.lcol[k], w.lw[k], w.lK, w.lS, w.pkeys, w.pvals};
+    hipLaunchKernelGGL(k_f_aggregate_big, dim3(std::min(nc, 256)), dim3(kFWide), 0, st, A);
+    hipLaunchKernelGGL(k_f_aggregate, dim3(std::min(nc, 8192)), dim3(kBlock), 0, st, A);
     // the aggregate read the level's memberships (w.lC past the first pass)
     launch_iota_i32(w.lC, nc, st);
     launch_fill_i32(w.size, 1, nc, st);
@@ -1296,11 +1492,12 @@ lv_status run_f(bool df, const lv_graph_f* g, const lv_edges_f* del, const lv_ed
   if (aggregated) {
     launch_lookup(state->C, N, Cl, st);
     hipLaunchKernelGGL(k_f_zero_d, dim3(blocks(N)), dim3(kBlock), 0, st, state->Sigma, static_cast<int64_t>(N));
-    hipLaunchKernelGGL(k_f_sigma, dim3(blocks(N)), dim3(kBlock), 0, st, state->C, state->K, N, state->Sigma);
+    hipLaunchKernelGGL(k_f_sigma, dim3(std::min(256, N / 4096 + 1)), dim3(kFWide), 0, st, state->C, state->K, N,
+                       state->Sigma);
     if (state->size) launch_community_sizes(state->C, N, state->size, st);
     F_HIP(hipGetLastError());
   }
-  F_HIP(hipStreamSynchronize(st));
+  if (aggregated) F_HIP(hipStreamSynchronize(st));  // (else the last iteration's read waited)
   S.seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
   return LV_OK;
 }
@@ -1426,9 +1623,8 @@ lv_status modularity_f(const lv_graph_f* g, const int32_t* C, double* q_host, vo
   hipLaunchKernelGGL(k_f_totals, dim3(blocks(n)), dim3(kBlock), 0, st, C, w.lK, n, w.tot, w.ctr);
   hipLaunchKernelGGL(k_f_sumsq, dim3(blocks(n, 4096)), dim3(kBlock), 0, st, w.tot, n, w.ctr);
   F_HIP(hipGetLastError());
-  double two_m = 0.0;
-  F_HIP(hipMemcpyAsync(&two_m, g->two_m, sizeof(double), hipMemcpyDeviceToHost, st));
   if ((s = read(w, rd, st))) return s;
+  const double two_m = rd.two_m;
   if (rd.err) return lv_fail(LV_EINVAL, "a membership lies outside [0, n)");
   if (!(two_m > 0.0)) return lv_fail(LV_EEMPTY, "graph has no edges (2m = 0)");
   *q_host = intra / two_m - rd.sum / (two_m * two_m);

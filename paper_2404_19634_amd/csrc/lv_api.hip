@@ -77,6 +77,7 @@ lv_status pinned(int64_t** out) {
   *out = g_pinned.p;
   return LV_OK;
 }
+static_assert(sizeof(int64_t) * kHostTotal >= kPlanArcs + 8 * kPlanKeys, "a plan with its arcs fits");
 
 // ---- measurement hook (lv_set_timing) ------------------------------------
 std::atomic<uint32_t> g_timed_mask{0};
@@ -289,6 +290,7 @@ lv_tuning effective_tuning() {
 }  // namespace
 
 lv_tuning lv_effective_tuning() { return effective_tuning(); }
+lv_status lv_pinned_host(int64_t** out) { return pinned(out); }
 
 namespace {
 

@@ -691,6 +691,8 @@ void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st);
 // ASYNC iteration.
 lv_status lv_fail(lv_status code, const char* msg);
 lv_tuning lv_effective_tuning();
+// The calling thread's pinned readback buffer (room for a plan with its arcs).
+lv_status lv_pinned_host(int64_t** out);
 PlanKeys lv_plan_keys(const std::vector<SubRound>& plan, const lv_tuning& tu);
 std::vector<SubRound> lv_sub_rounds(int32_t mode, int32_t pass, int64_t est_frontier, int32_t n,
                                     const lv_tuning& tu);
