@@ -654,7 +654,7 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
   FrontList cur_fl = front_list(ws, 0), next_fl = front_list(ws, 1);
   double tau = p->tolerance;
   bool aggregated = false;
-  bool moved_dirty = false;  // cleared by the first kernel, then by the SYNC apply unless pulled
+  bool flags_clear = false;  // ws.push_flags
   int64_t iter_seq = 0, round_seq = 0;  // select the alternating counter sets
   int64_t two_m = 0;
   float ms_mark = 0.f, ms_move = 0.f, ms_agg = 0.f;
@@ -674,7 +674,6 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     a.mode = p->mode;
     a.guard = p->swap_guard;
     a.wave_max = tu.wave_max_degree;
-    const int64_t words_l = (static_cast<int64_t>(L.n) + 31) / 32;
     // upper bound of the frontier size, for the choice of sub-rounds
     int64_t est_frontier = L.n;
     if (pass == 0 && ap == A_DF) est_frontier = 2 * (D.count + I.count);
@@ -692,10 +691,6 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       const bool pull = est_frontier > L.n / 4;
       a.push = pull ? 0 : 1;
       a.moved = (pull || p->mode == LV_SYNC) ? ws.moved : nullptr;
-      if (a.moved && moved_dirty) {
-        LV_HIP(hipMemsetAsync(ws.moved, 0, sizeof(uint32_t) * words_l, st));
-        moved_dirty = false;
-      }
       int64_t* sc = ws.ctr + CTR_STATS0 + (iter_seq & 1) * kStatSet;
       int64_t* sc_next = ws.ctr + CTR_STATS0 + ((iter_seq + 1) & 1) * kStatSet;
       const std::vector<SubRound> plan = sub_rounds(p->mode, pass, est_frontier, L.n, tu);
@@ -735,8 +730,10 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
       }
       if (p->mode == LV_SYNC) launch_apply_moves(a, ws, !pull, st);
       if (pull) {
-        launch_pull_expand(a, ws, st);
-        moved_dirty = true;
+        if (!flags_clear)  // (every expansion leaves them so)
+          LV_HIP(hipMemsetAsync(ws.push_flags, 0, static_cast<size_t>(ws.words) * 32, st));
+        flags_clear = true;
+        launch_expand(a, ws, st);
       }
       LV_CHECK_LAUNCH();
       std::swap(cur, next);

@@ -685,7 +685,7 @@ uint32_t bins_for_degrees(int32_t lo, int32_t hi, int32_t wave_max);
 void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
                   bool expand, hipStream_t st);
 void launch_apply_moves(const MoveArgs& a, Workspace& ws, bool clear_moved, hipStream_t st);
-void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st);
+void launch_expand(const MoveArgs& a, Workspace& ws, hipStream_t st);
 // Host helpers shared with the paper-precision path (fp.hip): the error
 // message of lv_last_error, the tuning in force, and the sub-rounds of an
 // ASYNC iteration.

@@ -1500,15 +1500,21 @@ constexpr size_t lds_table() {
   return sizeof(Red) + 2 * sizeof(int32_t) * kBlockTS + sizeof(int32_t) * (kHubMaxSegs + 1);
 }
 
-// ONLY == NBINS: the fused kernel, whose workgroups find their role from the
-// block ranges laid end to end.  ONLY < NBINS: that role alone over the
-// whole grid (its own register and LDS budget, so a higher occupancy).
+// ONLY == kAllRoles, kSmallRoles (the roles up to 32 arcs a row) and
+// kShortRoles (those and the wavefront's): kernels whose workgroups find
+// their role from the block ranges laid end to end.
+// ONLY < NBINS: that role alone over the whole grid (its own register and LDS
+// budget, so a higher occupancy).
+constexpr int kAllRoles = NBINS, kSmallRoles = NBINS + 1, kShortRoles = NBINS + 2;
 template <int TS, int ONLY>
 __global__ void __launch_bounds__(kBlock) k_move_all(Dev D, Bins bins, Roles R, HubIn H) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int64_t two_m = load_two_m(D);
   if (two_m == 0) return;
-  constexpr bool kAny = ONLY == NBINS;
+  constexpr bool kAny = ONLY >= NBINS;
+  constexpr bool kSmall = kAny || ONLY <= BIN_G32;
+  constexpr bool kWaves = ONLY == kAllRoles || ONLY == kShortRoles || ONLY == BIN_WAVE;
+  constexpr bool kBlocks = ONLY == kAllRoles || ONLY == BIN_BLOCK;
   int role = ONLY;
   int64_t rb = blockIdx.x, nb = gridDim.x;
   if constexpr (kAny) {
@@ -1520,7 +1526,7 @@ __global__ void __launch_bounds__(kBlock) k_move_all(Dev D, Bins bins, Roles R, 
     nb = R.end[r] - lo;
     role = NBINS - 1 - r;
   }
-  if ((kAny || ONLY <= BIN_G32) && role <= BIN_G32) {
+  if (kSmall && role <= BIN_G32) {
     MoveAgg* agg = reinterpret_cast<MoveAgg*>(smem);
     agg_begin(agg);
     switch (role) {
@@ -1530,20 +1536,20 @@ __global__ void __launch_bounds__(kBlock) k_move_all(Dev D, Bins bins, Roles R, 
       default: role_small<32>(D, two_m, bins.list[BIN_G32], BIN_G32, rb, nb, agg); break;
     }
     agg_end_moves(agg, D, two_m);
-  } else if ((kAny || ONLY == BIN_WAVE) && role == BIN_WAVE) {
+  } else if (kWaves && role == BIN_WAVE) {
     MoveAgg* agg = reinterpret_cast<MoveAgg*>(smem);
     int32_t* keys = reinterpret_cast<int32_t*>(smem + sizeof(MoveAgg));
     int32_t* vals = keys + (kBlock / kWave) * TS;
     agg_begin(agg);
     role_wave<TS>(D, two_m, bins.list[BIN_WAVE], rb, nb, keys, vals, agg);
     agg_end_moves(agg, D, two_m);
-  } else if ((kAny || ONLY == BIN_BLOCK) && role == BIN_BLOCK) {
+  } else if (kBlocks && role == BIN_BLOCK) {
     Red* red = reinterpret_cast<Red*>(smem);
     int32_t* keys = reinterpret_cast<int32_t*>(smem + sizeof(Red));
     agg_begin(&red->agg);
     role_block(D, two_m, bins.list[BIN_BLOCK], rb, nb, keys, keys + kBlockTS, red);
     agg_end_moves(&red->agg, D, two_m);
-  } else if (kAny || ONLY == BIN_HUB) {
+  } else if (ONLY == kAllRoles || ONLY == BIN_HUB) {
     Red* red = reinterpret_cast<Red*>(smem);
     int32_t* tk = reinterpret_cast<int32_t*>(smem + sizeof(Red));
     role_hub_insert(D, H, rb, nb, tk, tk + kHubTS, tk + 2 * kHubTS, red);
@@ -1835,126 +1841,121 @@ __global__ void __launch_bounds__(kBlock) k_apply_moves(int32_t* __restrict__ C,
 }
 
 // --------------------------------------------------------------------------
-// Pull expansion: vertex j joins the next frontier iff a neighbour i != j
-// moved.  The graph is symmetric, so this is the same set the movers would
-// push, without one atomic per arc.  A wavefront owns one 32-vertex word
-// (4 groups of 16 lanes, 8 rows each) and stores it whole; rows longer
-// than kPullGroupMax are left to a workgroup each, which ORs its bit in.
+// The next frontier of a large iteration: vertex j joins iff a neighbour
+// i != j moved.  Pull reads every row until it meets a mover; push flags the
+// neighbours of every mover.  The graph is symmetric, so both give the set
+// the movers would push one atomic per arc.  Once the scan is done the
+// iteration's statistics say which costs less: push when the movers' arcs are
+// under an eighth of the arcs scanned.  Three launches either way: by words
+// of 32 vertices, the long rows a workgroup each, and the end, which packs
+// the pushed flags and leaves flags, movers and the list of long rows clear
+// for the next iteration.  (Five launches and three fills before.)
 // --------------------------------------------------------------------------
 constexpr int kPullGroup = 16;
+constexpr int kPullLane = 16;       // arcs of a row that its own lane reads
 constexpr int kPullGroupMax = 2048;
-
-// Pull or push: the expansion reads every row until it meets a mover
-// (pull), or ORs in the neighbours of every mover (push).  Once the scan is
-// done the iteration's statistics say which costs less: push when the
-// movers' arcs are under an eighth of the arcs scanned.
 constexpr int64_t kPushRatio = 8;
+constexpr int32_t kPushShortMax = 256;
 
 __device__ __forceinline__ int64_t stat_sum(const int64_t* sc, int st) {
   int64_t v = 0;
   for (int r = 0; r < kStatReplicas; ++r) v += sc[r * kStatStride + st];
   return v;
 }
-
 __device__ __forceinline__ bool expand_by_push(const int64_t* sc) {
   return stat_sum(sc, ST_EXPAND) * kPushRatio < stat_sum(sc, ST_ARCS);
 }
 
-__global__ void __launch_bounds__(kBlock) k_pull_words(const int64_t* __restrict__ row_start,
-                                                      const int32_t* __restrict__ row_len,
-                                                      const int32_t* __restrict__ col, int32_t n,
-                                                      const uint32_t* __restrict__ moved, uint32_t* __restrict__ next,
-                                                      int32_t* __restrict__ longlist, int64_t* __restrict__ ctr,
-                                                      const int64_t* __restrict__ sc, int64_t* __restrict__ next_cnt) {
-  // either way (pull here, or the push kernels) the next frontier is built
-  // without its list
-  if (blockIdx.x == 0 && threadIdx.x == 0) *next_cnt = kFlInvalid;
-  if (expand_by_push(sc)) return;
+struct Expand {
+  const int64_t* row_start;
+  const int32_t* row_len;
+  const int32_t* col;
+  int32_t n;
+  uint32_t* moved;
+  uint32_t* next;
+  uint8_t* flags;     // one byte per vertex, all zero between iterations
+  int32_t* longlist;  // ctr[CTR_AUX0] rows (that counter is the expansion's alone)
+  int64_t* ctr;
+  const int64_t* sc;
+};
+
+// Pull, two words to a wavefront: a lane reads the first arcs of its own row
+// (eight in flight: what decides most rows while many vertices move), then
+// groups of 16 lanes take the rows still undecided, four at a time.  Rows
+// over kPullGroupMax are left to a workgroup each.  (A group of 16 lanes per
+// row from its first arc, eight rows one after another: 71 us for 700,000
+// rows of 24 arcs, a chain of three loads per row; this: 22 us.)
+__device__ __forceinline__ void pull_words(const Expand& X) {
   const int lane = lane_id();
-  const int grp = lane / kPullGroup;
-  const int sub = lane % kPullGroup;
-  const int64_t words = (static_cast<int64_t>(n) + 31) / 32;
+  const int grp = lane / kPullGroup, sub = lane % kPullGroup;
+  const int64_t words = (static_cast<int64_t>(X.n) + 31) / 32;
   const int64_t wave = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) / kWave;
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
-  for (int64_t w = wave; w < words; w += nwaves) {
-    uint32_t word = 0;
-    for (int r = 0; r < 8; ++r) {
-      const int bit = grp * 8 + r;
-      const int64_t j = w * 32 + bit;
-      bool hit = false;
-      if (j < n) {
-        const int32_t len = row_len[j];
-        if (len > kPullGroupMax) {
-          if (sub == 0) {
-            const int64_t pos = static_cast<int64_t>(
-                atomicAdd(reinterpret_cast<unsigned long long*>(&ctr[CTR_AUX1]), 1ull));
-            longlist[pos] = static_cast<int32_t>(j);
-          }
-        } else {
-          const int64_t s = row_start[j];
-          for (int32_t k = sub; k < len && !hit; k += kPullGroup) {
-            const int32_t i = col[s + k];
-            hit = i != j && test_bit(moved, i);
-          }
+  for (int64_t p = wave; 2 * p < words; p += nwaves) {
+    const int64_t j = p * kWave + lane;
+    int32_t len = j < X.n ? X.row_len[j] : 0;
+    const int64_t s = j < X.n ? X.row_start[j] : 0;
+    if (len > kPullGroupMax) {
+      const int64_t pos = static_cast<int64_t>(
+          atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_AUX0]), 1ull));
+      X.longlist[pos] = static_cast<int32_t>(j);
+      len = 0;
+    }
+    bool hit = false;
+    for (int32_t k0 = 0; k0 < kPullLane; k0 += 8) {
+      if (!__any(!hit && k0 < len)) break;
+      int32_t is[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) is[q] = !hit && k0 + q < len ? X.col[s + k0 + q] : static_cast<int32_t>(j);
+      bool h = false;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) h |= is[q] != j && test_bit(X.moved, is[q]);
+      hit |= h;
+    }
+    for (uint64_t todo = __ballot(!hit && len > kPullLane); todo;) {
+      // group g takes the g-th undecided row
+      uint64_t t = todo;
+      for (int q = 0; q < grp; ++q) t &= t - 1;
+      const int row = t ? __ffsll(static_cast<unsigned long long>(t)) - 1 : 0;
+      const int64_t rs = __shfl(s, row);
+      int32_t rl = __shfl(len, row);
+      if (!t) rl = 0;
+      const int64_t rj = p * kWave + row;
+      bool found = false;
+      for (int32_t k = kPullLane; __any(!found && k < rl); k += 2 * kPullGroup) {
+        bool h = false;
+        if (!found) {
+          const int32_t a = k + sub < rl ? X.col[rs + k + sub] : static_cast<int32_t>(rj);
+          const int32_t b = k + kPullGroup + sub < rl ? X.col[rs + k + kPullGroup + sub] : static_cast<int32_t>(rj);
+          h = (a != rj && test_bit(X.moved, a)) || (b != rj && test_bit(X.moved, b));
         }
+        found |= ((__ballot(h) >> (grp * kPullGroup)) & 0xFFFFull) != 0;
       }
-      // any lane of the group found a moved neighbour
-      const uint64_t m = __ballot(hit);
-      if ((m >> (grp * kPullGroup)) & 0xFFFFull) word |= 1u << bit;
+      // lane `row` learns its group's answer
+      const uint64_t f = __ballot(found && sub == 0);
+      for (int g = 0; g < kWave / kPullGroup && todo; ++g) {
+        const int r = __ffsll(static_cast<unsigned long long>(todo)) - 1;
+        if (lane == r && ((f >> (g * kPullGroup)) & 1u)) hit = true;
+        todo &= todo - 1;
+      }
     }
-    // groups hold disjoint bits of the word
-    word |= __shfl_xor(word, 16);
-    word |= __shfl_xor(word, 32);
-    if (lane == 0) next[w] = word;
-  }
-}
-
-__global__ void __launch_bounds__(kBlock) k_pull_long(const int64_t* __restrict__ row_start,
-                                                     const int32_t* __restrict__ row_len,
-                                                     const int32_t* __restrict__ col,
-                                                     const uint32_t* __restrict__ moved, uint32_t* __restrict__ next,
-                                                     const int32_t* __restrict__ longlist, const int64_t* __restrict__ ctr,
-                                                     const int64_t* __restrict__ sc) {
-  __shared__ int s_hit;
-  if (expand_by_push(sc)) return;
-  const int64_t count = ctr[CTR_AUX1];
-  for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
-    const int32_t j = longlist[idx];
-    if (threadIdx.x == 0) s_hit = 0;
-    __syncthreads();
-    const int64_t s = row_start[j];
-    const int32_t len = row_len[j];
-    for (int32_t k = threadIdx.x; k < len; k += kBlock) {
-      if (s_hit) break;
-      const int32_t i = col[s + k];
-      if (i != j && test_bit(moved, i)) s_hit = 1;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_hit) set_bit(next, j);
-    __syncthreads();
+    const uint64_t m = __ballot(hit);
+    if (lane == 0) X.next[2 * p] = static_cast<uint32_t>(m);
+    if (lane == 32 && 2 * p + 1 < words) X.next[2 * p + 1] = static_cast<uint32_t>(m >> 32);
   }
 }
 
 // Push: one wavefront per word of the movers bitmask flags the neighbours
 // of its movers whose rows are short, a lane per arc; longer rows are
 // queued for a workgroup each.  Flags are byte stores (idempotent, no
-// read-modify-write at the memory side, unlike a bitmask atomicOr per arc);
-// a last kernel packs them into the next frontier's words.
-constexpr int32_t kPushShortMax = 256;
-
-__global__ void __launch_bounds__(kBlock) k_push_words(const int64_t* __restrict__ row_start,
-                                                      const int32_t* __restrict__ row_len,
-                                                      const int32_t* __restrict__ col, int32_t n,
-                                                      const uint32_t* __restrict__ moved, uint8_t* __restrict__ flags,
-                                                      int32_t* __restrict__ longlist, int64_t* __restrict__ ctr,
-                                                      const int64_t* __restrict__ sc) {
-  if (!expand_by_push(sc)) return;
+// read-modify-write at the memory side, unlike a bitmask atomicOr per arc).
+__device__ __forceinline__ void push_words(const Expand& X) {
   const int lane = lane_id();
-  const int64_t words = (static_cast<int64_t>(n) + 31) / 32;
+  const int64_t words = (static_cast<int64_t>(X.n) + 31) / 32;
   const int64_t wave = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) / kWave;
   const int64_t nwaves = static_cast<int64_t>(gridDim.x) * blockDim.x / kWave;
   for (int64_t w = wave; w < words; w += nwaves) {
-    const uint32_t bits = moved[w];
+    const uint32_t bits = X.moved[w];
     if (!bits) continue;
     // each lane of the first 32 loads one mover's row; then the wavefront
     // walks the short rows together
@@ -1963,12 +1964,12 @@ __global__ void __launch_bounds__(kBlock) k_push_words(const int64_t* __restrict
     int32_t len = 0;
     int64_t s = 0;
     if (mine) {
-      len = row_len[i];
-      s = row_start[i];
+      len = X.row_len[i];
+      s = X.row_start[i];
       if (len > kPushShortMax) {
         const int64_t pos =
-            static_cast<int64_t>(atomicAdd(reinterpret_cast<unsigned long long*>(&ctr[CTR_AUX1]), 1ull));
-        longlist[pos] = i;
+            static_cast<int64_t>(atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_AUX0]), 1ull));
+        X.longlist[pos] = i;
         len = 0;
       }
     }
@@ -1978,46 +1979,73 @@ __global__ void __launch_bounds__(kBlock) k_push_words(const int64_t* __restrict
       const int32_t vl = __shfl(len, b);
       const int64_t vs = __shfl(s, b);
       for (int32_t k = lane; k < vl; k += kWave) {
-        const int32_t j = col[vs + k];
-        if (j != v) flags[j] = 1;
+        const int32_t j = X.col[vs + k];
+        if (j != v) X.flags[j] = 1;
       }
     }
   }
 }
 
-__global__ void __launch_bounds__(kBlock) k_push_long(const int64_t* __restrict__ row_start,
-                                                     const int32_t* __restrict__ row_len,
-                                                     const int32_t* __restrict__ col, uint8_t* __restrict__ flags,
-                                                     const int32_t* __restrict__ longlist,
-                                                     const int64_t* __restrict__ ctr, const int64_t* __restrict__ sc) {
-  if (!expand_by_push(sc)) return;
-  const int64_t count = ctr[CTR_AUX1];
+__global__ void __launch_bounds__(kBlock) k_expand_words(Expand X, int64_t* __restrict__ next_cnt) {
+  const bool push = expand_by_push(X.sc);
+  // either way the next frontier is built without its list
+  if (blockIdx.x == 0 && threadIdx.x == 0) *next_cnt = kFlInvalid;
+  if (push)
+    push_words(X);
+  else
+    pull_words(X);
+}
+
+__global__ void __launch_bounds__(kBlock) k_expand_long(Expand X) {
+  __shared__ int s_hit;
+  const int64_t count = X.ctr[CTR_AUX0];
+  if (blockIdx.x >= count) return;
+  const bool push = expand_by_push(X.sc);
   for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
-    const int32_t i = longlist[idx];
-    const int64_t s = row_start[i];
-    const int32_t len = row_len[i];
-    for (int32_t k = threadIdx.x; k < len; k += kBlock) {
-      const int32_t j = col[s + k];
-      if (j != i) flags[j] = 1;
+    const int32_t j = X.longlist[idx];
+    const int64_t s = X.row_start[j];
+    const int32_t len = X.row_len[j];
+    if (push) {
+      for (int32_t k = threadIdx.x; k < len; k += kBlock) {
+        const int32_t i = X.col[s + k];
+        if (i != j) X.flags[i] = 1;
+      }
+      continue;
     }
+    if (threadIdx.x == 0) s_hit = 0;
+    __syncthreads();
+    for (int32_t k = threadIdx.x; k < len; k += kBlock) {
+      if (s_hit) break;
+      const int32_t i = X.col[s + k];
+      if (i != j && test_bit(X.moved, i)) s_hit = 1;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && s_hit) set_bit(X.next, j);
+    __syncthreads();
   }
 }
 
-// The pushed flags of 32 vertices become one word of the next frontier.
-__global__ void __launch_bounds__(kBlock) k_push_pack(const uint8_t* __restrict__ flags, uint32_t* __restrict__ next,
-                                                     int64_t words, const int64_t* __restrict__ sc) {
-  if (!expand_by_push(sc)) return;
+// The pushed flags of 32 vertices become one word of the next frontier;
+// flags, movers and the list's count are cleared.
+__global__ void __launch_bounds__(kBlock) k_expand_end(Expand X, int64_t words) {
+  const bool push = expand_by_push(X.sc);
+  if (blockIdx.x == 0 && threadIdx.x == 0) X.ctr[CTR_AUX0] = 0;
   for (int64_t w = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; w < words;
        w += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const uint4* f = reinterpret_cast<const uint4*>(flags + w * 32);
+    X.moved[w] = 0;
+    if (!push) continue;
+    uint4* f = reinterpret_cast<uint4*>(X.flags + w * 32);
     const uint4 lo = f[0], hi = f[1];
+    const uint4 z = {0, 0, 0, 0};
+    f[0] = z;
+    f[1] = z;
     const uint32_t part[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     uint32_t bits = 0;
 #pragma unroll
     for (int q = 0; q < 8; ++q)
 #pragma unroll
       for (int b = 0; b < 4; ++b) bits |= ((part[q] >> (8 * b)) & 0xFFu ? 1u : 0u) << (4 * q + b);
-    next[w] = bits;
+    X.next[w] = bits;
   }
 }
 
@@ -2083,6 +2111,24 @@ void launch_call_begin(Workspace& ws, const int64_t* two_m, bool dense_a, bool k
 
 void launch_publish(const Workspace& ws, const int64_t* sc, int64_t* dst, hipStream_t st) {
   hipLaunchKernelGGL(k_publish, dim3(1), dim3(kBlock), 0, st, ws.ctr, sc, dst);
+}
+
+// The roles up to `hi` of the mask in one launch.
+constexpr int64_t kGroupRows = 16384;
+template <int TS, int GROUP>
+void launch_group(uint32_t mask, int hi, const Dev& D, const Bins& b, const HubIn& H, size_t lds, const int* per,
+                  hipStream_t st) {
+  Roles R;
+  int64_t end = 0;
+  for (int r = 0; r < NBINS; ++r) {
+    const int k = NBINS - 1 - r;
+    if (k <= hi && ((mask >> k) & 1u)) end += per[k];
+    R.end[r] = end;
+  }
+  if (!end) return;
+  const TimerPair tp = timer_pair(LV_TIME_SCAN);
+  hipExtLaunchKernelGGL((k_move_all<TS, GROUP>), dim3(static_cast<unsigned>(end)), dim3(kBlock),
+                        static_cast<uint32_t>(lds), st, tp.start, tp.stop, 0, D, b, R, H);
 }
 
 FrontList front_list(const Workspace& ws, int k) {
@@ -2177,6 +2223,36 @@ void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const Sc
     else
       launch_move_all<1024>(D, b, R, H, lds, tp, st);
   } else {
+    // SYNC decisions see no move of their iteration, so the short roles share
+    // a launch: one of few rows is bound by its chain of loads, and the chains
+    // overlap.  (700,000-vertex R-MAT graph, bins of 4 / 8 / 16 / 32 arcs
+    // 16 + 14 + 15 + 25 us apart, 59 us together; the workgroup and hub roles
+    // 61 + 31 us apart, 111 us together, each with half of the device.)
+    // So do an ASYNC sub-round's up to the wavefront's where it is a small
+    // part of the level, its vertices rarely meeting (static run on a
+    // 300,000-vertex power-law graph 24.3 -> 21.1 ms, on a 100,000-vertex SBM
+    // graph 9.0 -> 8.0; modularity within 1e-4 on eight graphs; past kGroupRows
+    // the launches are bound by their arcs: 4 ms of 56 at 3 million vertices
+    // with it, no more at four times the limit).  Longer rows keep their own
+    // launches: together with the rest they cost a 2^20-vertex R-MAT graph
+    // 0.0023 of a modularity of 0.0742.
+    int64_t rows = 0;
+    for (int k = 0; k <= BIN_WAVE; ++k) rows += std::max<int64_t>(S.cnt[k], 0);
+    const bool part = a.mode != LV_SYNC && S.cnt[0] >= 0 && rows * 8 <= a.g.n;
+    if (part && rows <= kGroupRows) {
+      if (ts <= 128)
+        launch_group<128, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
+      else if (ts <= 256)
+        launch_group<256, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
+      else if (ts <= 512)
+        launch_group<512, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
+      else
+        launch_group<1024, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
+      bin_mask &= ~((2u << BIN_WAVE) - 1u);
+    } else if (a.mode == LV_SYNC) {
+      launch_group<128, kSmallRoles>(bin_mask, BIN_G32, D, b, H, sizeof(MoveAgg), per, st);
+      bin_mask &= ~((2u << BIN_G32) - 1u);
+    }
     for (int k = 0; k < NBINS; ++k) {
       if (!(bin_mask & (1u << k))) continue;
       const TimerPair tp = timer_pair(LV_TIME_SCAN);
@@ -2244,22 +2320,15 @@ void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const S
   launch_scan(a, ws, tu, S, bin_mask, st);
 }
 
-void launch_pull_expand(const MoveArgs& a, Workspace& ws, hipStream_t st) {
+void launch_expand(const MoveArgs& a, Workspace& ws, hipStream_t st) {
   const int64_t words = (static_cast<int64_t>(a.g.n) + 31) / 32;
-  (void)hipMemsetAsync(ws.ctr + CTR_AUX1, 0, sizeof(int64_t), st);
-  hipLaunchKernelGGL(k_pull_words, dim3(grid_for(words * kWave, kBlock, 8192)), dim3(kBlock), 0, st, a.g.row_start,
-                     a.g.row_len, a.g.col, a.g.n, a.moved, a.next, ws.bins[NBINS - 1] + 0, ws.ctr, a.sc,
+  const Expand X{a.g.row_start, a.g.row_len, a.g.col, a.g.n, a.moved, a.next, ws.push_flags, ws.bins[NBINS - 1],
+                 ws.ctr, a.sc};
+  hipLaunchKernelGGL(k_expand_words, dim3(grid_for(words * kWave / 2, kBlock, 8192)), dim3(kBlock), 0, st, X,
                      a.next_fl.cnt);
-  hipLaunchKernelGGL(k_pull_long, dim3(1024), dim3(kBlock), 0, st, a.g.row_start, a.g.row_len, a.g.col, a.moved,
-                     a.next, ws.bins[NBINS - 1] + 0, ws.ctr, a.sc);
-  // (only one of the pair above and the three below does any work)
-  (void)hipMemsetAsync(ws.push_flags, 0, static_cast<size_t>(words) * 32, st);
-  hipLaunchKernelGGL(k_push_words, dim3(grid_for(words * kWave, kBlock, 8192)), dim3(kBlock), 0, st, a.g.row_start,
-                     a.g.row_len, a.g.col, a.g.n, a.moved, ws.push_flags, ws.bins[NBINS - 1] + 0, ws.ctr, a.sc);
-  hipLaunchKernelGGL(k_push_long, dim3(1024), dim3(kBlock), 0, st, a.g.row_start, a.g.row_len, a.g.col,
-                     ws.push_flags, ws.bins[NBINS - 1] + 0, ws.ctr, a.sc);
-  hipLaunchKernelGGL(k_push_pack, dim3(grid_for(words, kBlock, 4096)), dim3(kBlock), 0, st, ws.push_flags, a.next,
-                     words, a.sc);
+  hipLaunchKernelGGL(k_expand_long, dim3(static_cast<unsigned>(std::min<int64_t>(a.g.n, 1024))), dim3(kBlock), 0, st,
+                     X);
+  hipLaunchKernelGGL(k_expand_end, dim3(grid_for(words, kBlock, 4096)), dim3(kBlock), 0, st, X, words);
 }
 
 void launch_apply_moves(const MoveArgs& a, Workspace& ws, bool clear_moved, hipStream_t st) {

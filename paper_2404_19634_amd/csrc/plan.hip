@@ -267,34 +267,40 @@ __global__ void __launch_bounds__(kBlock) k_plan_fill(Frontier f, PlanKeys pk, P
 
 // Hub rows of sub-round blockIdx.x: table offsets (each sub-round uses the
 // pool from its start), units, and zero sums.  Units of all sub-rounds lie
-// one after another (reserved with one atomic each).
-__global__ void __launch_bounds__(kBlock) k_plan_hubs(PlanBuf p, PlanLists L, int32_t rounds,
-                                                     const int32_t* __restrict__ row_len, HubOut H,
-                                                     int64_t* __restrict__ hub_kid, int64_t* __restrict__ rc) {
-  __shared__ int64_t s_off[kBlock];
-  __shared__ int32_t s_u[kBlock], s_c[kBlock];
+// one after another (reserved with one atomic each).  NT threads: 1024 where
+// one workgroup has the whole frontier's hubs (some thousands on a
+// 700,000-vertex R-MAT graph: 22 us with 256 threads and LDS scans, 11 so),
+// 256 where there is a workgroup per sub-round.
+template <int NT>
+__global__ void __launch_bounds__(NT) k_plan_hubs(PlanBuf p, PlanLists L, int32_t rounds,
+                                                 const int32_t* __restrict__ row_len, HubOut H,
+                                                 int64_t* __restrict__ hub_kid, int64_t* __restrict__ rc) {
+  constexpr int NW = NT / kWave;
+  __shared__ int64_t s_wo[NW], s_wu[NW];  // the wavefronts' sums: slots; units | clear units << 32
+  __shared__ int32_t s_u[NT], s_c[NT];    // inclusive sums of a chunk
   __shared__ int32_t s_before, s_ub, s_cb, s_ut, s_ct;
   const int r = blockIdx.x;
   const int key = r * kKeySlots + BIN_HUB;
+  const int lane = lane_id(), wv = threadIdx.x / kWave;
   const int32_t count = p.cnt[key];
   if (count == 0) return;
   if (threadIdx.x == 0) s_before = s_ut = s_ct = 0;
   __syncthreads();
-  for (int q = threadIdx.x; q < r; q += kBlock) {
+  for (int q = threadIdx.x; q < r; q += NT) {
     const int32_t c = p.cnt[q * kKeySlots + BIN_HUB];
     if (c) atomicAdd(&s_before, c);
   }
   // (the key's list range ends at the cursor that placed it)
   const int32_t* list = L.list[BIN_HUB] + (p.cursor[key] - count);
   int32_t ut = 0, ct = 0;
-  for (int32_t k = threadIdx.x; k < count; k += kBlock) {
+  for (int32_t k = threadIdx.x; k < count; k += NT) {
     const int32_t deg = row_len[list[k]];
     ut += static_cast<int32_t>(hub_units(deg));
     ct += static_cast<int32_t>(hub_cunits(deg));
   }
   ut = wave_sum_i32(ut);
   ct = wave_sum_i32(ct);
-  if (lane_id() == 0) {
+  if (lane == 0) {
     atomicAdd(&s_ut, ut);
     atomicAdd(&s_ct, ct);
   }
@@ -316,30 +322,41 @@ __global__ void __launch_bounds__(kBlock) k_plan_hubs(PlanBuf p, PlanLists L, in
   const int64_t hb = s_before;
   int64_t off0 = 0;
   int32_t u0 = 0, c0 = 0;
-  for (int32_t k0 = 0; k0 < count; k0 += kBlock) {
+  for (int32_t k0 = 0; k0 < count; k0 += NT) {
     const int32_t k = k0 + threadIdx.x;
-    const int32_t m = min(kBlock, count - k0);
+    const int32_t m = min(NT, count - k0);
     const int32_t deg = k < count ? row_len[list[k]] : 0;
     const int64_t sl = k < count ? hub_slots(deg) : 0;
     const int32_t nu = k < count ? static_cast<int32_t>(hub_units(deg)) : 0;
     const int32_t nc = k < count ? static_cast<int32_t>(hub_cunits(deg)) : 0;
-    s_off[threadIdx.x] = sl;
-    s_u[threadIdx.x] = nu;
-    s_c[threadIdx.x] = nc;
-    __syncthreads();
-    for (int d = 1; d < m; d <<= 1) {
-      const bool on = static_cast<int>(threadIdx.x) >= d;
-      const int64_t a0 = on ? s_off[threadIdx.x - d] : 0;
-      const int32_t a1 = on ? s_u[threadIdx.x - d] : 0, a2 = on ? s_c[threadIdx.x - d] : 0;
-      __syncthreads();
-      s_off[threadIdx.x] += a0;
-      s_u[threadIdx.x] += a1;
-      s_c[threadIdx.x] += a2;
-      __syncthreads();
+    int64_t io = sl, iu = (static_cast<int64_t>(nc) << 32) | nu;  // (sums stay under 2^31 each)
+    for (int d = 1; d < kWave; d <<= 1) {
+      const int64_t a = __shfl_up(io, d), b = __shfl_up(iu, d);
+      if (lane >= d) {
+        io += a;
+        iu += b;
+      }
     }
+    if (lane == kWave - 1) {
+      s_wo[wv] = io;
+      s_wu[wv] = iu;
+    }
+    __syncthreads();
+    int64_t to = 0, tu = 0;  // the chunk's sums
+    for (int q = 0; q < NW; ++q) {
+      if (q == wv) {
+        io += to;
+        iu += tu;
+      }
+      to += s_wo[q];
+      tu += s_wu[q];
+    }
+    s_u[threadIdx.x] = static_cast<int32_t>(iu);
+    s_c[threadIdx.x] = static_cast<int32_t>(iu >> 32);
+    __syncthreads();
     if (k < count) {
-      H.off[hb + k] = off0 + s_off[threadIdx.x] - sl;
-      H.cbase[hb + k] = c0 + s_c[threadIdx.x] - nc;
+      H.off[hb + k] = off0 + io - sl;
+      H.cbase[hb + k] = c0 + static_cast<int32_t>(iu >> 32) - nc;
       H.cnum[hb + k] = nc;
       hub_kid[hb + k] = 0;
     }
@@ -352,19 +369,20 @@ __global__ void __launch_bounds__(kBlock) k_plan_hubs(PlanBuf p, PlanLists L, in
       }
       return lo;
     };
-    for (int32_t x = threadIdx.x; x < s_u[m - 1]; x += kBlock) {
+    const int32_t cu = static_cast<int32_t>(tu), cc = static_cast<int32_t>(tu >> 32);
+    for (int32_t x = threadIdx.x; x < cu; x += NT) {
       const int q = owner(s_u, x);
       H.u_b[s_ub + u0 + x] = k0 + q;
       H.u_a[s_ub + u0 + x] = static_cast<int64_t>(x - (q ? s_u[q - 1] : 0)) * kHubUnitArcs;
     }
-    for (int32_t x = threadIdx.x; x < s_c[m - 1]; x += kBlock) {
+    for (int32_t x = threadIdx.x; x < cc; x += NT) {
       const int q = owner(s_c, x);
       H.c_b[s_cb + c0 + x] = k0 + q;
       H.c_s[s_cb + c0 + x] = static_cast<int64_t>(x - (q ? s_c[q - 1] : 0)) * kHubClearSlots;
     }
-    off0 += s_off[m - 1];
-    u0 += s_u[m - 1];
-    c0 += s_c[m - 1];
+    off0 += to;
+    u0 += cu;
+    c0 += cc;
     __syncthreads();
   }
 }
@@ -398,8 +416,12 @@ void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* tb, TimerPair
   hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kBlock), 0, st, pk, p, a.rc, a.sc);
   hipExtLaunchKernelGGL(k_plan_fill, dim3(grid), dim3(kBlock), 0, st, tb->start, tb->stop, 0, f, pk, p, L, a.ever,
                         a.sc);
-  if (a.hub_kid)
-    hipExtLaunchKernelGGL(k_plan_hubs, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, th->start,
+  if (!a.hub_kid) return;
+  if (pk.rounds == 1)
+    hipExtLaunchKernelGGL(k_plan_hubs<1024>, dim3(1), dim3(1024), 0, st, th->start, th->stop, 0, p, L, pk.rounds,
+                          a.row_len, a.hub, a.hub_kid, a.rc);
+  else
+    hipExtLaunchKernelGGL(k_plan_hubs<kBlock>, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, th->start,
                           th->stop, 0, p, L, pk.rounds, a.row_len, a.hub, a.hub_kid, a.rc);
 }
 
