@@ -159,8 +159,10 @@ __global__ void k_rank(Upd<W> U, BatchScratch b) {
 
 // per touched row: its length, its range in the partner list, its chunks
 // (one packed reservation, chunks << 32 | partners, per workgroup and pass
-// of kRowsPer rows per thread: the reservations all hit one counter).
-constexpr int kRowsPer = 4;
+// of kRowsPer rows per thread: the reservations all hit one counter; four rows
+// per thread leave too few workgroups: 20 us for 100,000 directions and 13 for
+// 32,000, two 14 and 10, one 14 and 11).
+constexpr int kRowsPer = 2;
 __global__ void __launch_bounds__(kBlock) k_rows(const int64_t* __restrict__ row_start,
                                                  const int32_t* __restrict__ row_len, BatchScratch b,
                                                  int64_t* __restrict__ ctr) {

@@ -501,7 +501,11 @@ __global__ void __launch_bounds__(kBlock) k_publish(const int64_t* __restrict__ 
 }
 
 constexpr int kBinStats = 3 + 2 * NBINS;  // processed, arcs, affected, per-bin vertices and arcs
-constexpr int kBinPer = 4;                // items (words or listed vertices) per thread per pass
+// Items (words or listed vertices) per thread per pass: the kernel is a chain
+// of memory round trips, shortest with one item and four times the workgroups
+// (100,000 listed vertices 29 us with four, 21 with two, 17 with one; 32,000:
+// 26, 20, 16).
+constexpr int kBinPer = 1;
 constexpr int kBinHubs = 2 * kBlock;      // hubs a workgroup reserves together per pass
 
 // --------------------------------------------------------------------------
