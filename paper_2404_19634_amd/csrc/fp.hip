@@ -72,14 +72,16 @@ __device__ __forceinline__ double wave_sum_d(double v) {
 __device__ __forceinline__ bool better_f(double g1, int32_t c1, double g0, int32_t c0) {
   return g1 > g0 || (g1 == g0 && c1 < c0);
 }
+template <int S = 1>
 __device__ __forceinline__ void wave_arg(double& g, int32_t& c) {
-  for (int s = 1; s < kWave; s <<= 1) {
-    const double og = __shfl_xor(g, s);
-    const int32_t oc = __shfl_xor(c, s);
+  if constexpr (S < kWave) {
+    const double og = other_half<S>(g);
+    const int32_t oc = other_half<S>(c);
     if (better_f(og, oc, g, c)) {
       g = og;
       c = oc;
     }
+    wave_arg<2 * S>(g, c);
   }
 }
 __device__ __forceinline__ bool weight_ok(float w) { return isfinite(w) && w > 0.0f; }

@@ -233,6 +233,44 @@ __device__ __forceinline__ int32_t wave_sum_i32(int32_t v) {
   return v;
 }
 
+// Exchanges between lanes of a row of 16 as DPP moves (a vector instruction
+// each, where __shfl takes a round through the LDS pipe).  All lanes of the
+// wavefront take part.
+template <int CTRL>
+__device__ __forceinline__ int32_t dpp(int32_t v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppXor3 = 0x1B;  // quad_perm
+constexpr int kDppMirror16 = 0x140, kDppMirror8 = 0x141;          // lane l of a group of 16 / 8 reads 15 - l / 7 - l
+constexpr int kDppRor = 0x120;                                    // + r: rotation by r lanes in 16
+
+// Step S of a reduction over 2 S lanes, after the steps before it: any lane
+// of the other half serves.
+template <int S>
+__device__ __forceinline__ int32_t other_half(int32_t v) {
+  if constexpr (S == 1) return dpp<kDppXor1>(v);
+  else if constexpr (S == 2) return dpp<kDppXor2>(v);
+  else if constexpr (S == 4) return dpp<kDppMirror8>(v);
+  else if constexpr (S == 8) return dpp<kDppMirror16>(v);
+  else return __shfl_xor(v, S);
+}
+template <int S>
+__device__ __forceinline__ int64_t other_half(int64_t v) {
+  const int32_t lo = other_half<S>(static_cast<int32_t>(v));
+  const int32_t hi = other_half<S>(static_cast<int32_t>(v >> 32));
+  return static_cast<int64_t>(static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32 | static_cast<uint32_t>(lo));
+}
+template <int S>
+__device__ __forceinline__ double other_half(double v) {
+  return __longlong_as_double(other_half<S>(static_cast<int64_t>(__double_as_longlong(v))));
+}
+// The sum over groups of G lanes, in every lane.
+template <int G, int S = 1, class T>
+__device__ __forceinline__ T group_sum(T v) {
+  if constexpr (S < G) return group_sum<G, 2 * S>(static_cast<T>(v + other_half<S>(v)));
+  else return v;
+}
+
 // Wave-aggregated append: lanes with `pred` get consecutive slots of
 // `list` after atomically bumping *count.  Returns the slot or -1.
 __device__ __forceinline__ int64_t wave_append(bool pred, int64_t* count) {

@@ -353,10 +353,11 @@ __global__ void __launch_bounds__(kBlock) k_hot_apply(int64_t* __restrict__ rc, 
 
 // Wavefront totals of gains, moves and mover arcs into the statistics.
 __device__ __forceinline__ void flush_totals(const Dev& D, int64_t gain, int64_t moved, int64_t arcs) {
-  gain = wave_sum_i64(gain);
-  moved = wave_sum_i64(moved);
-  arcs = wave_sum_i64(arcs);
-  if (lane_id() == 0 && moved) {
+  if (!__any(moved != 0)) return;
+  gain = group_sum<kWave>(gain);
+  moved = group_sum<kWave>(moved);
+  arcs = group_sum<kWave>(arcs);
+  if (lane_id() == 0) {
     stat_add(D.sc, ST_GAIN, gain);
     stat_add(D.sc, ST_EXPAND, arcs);
     stat_add(D.sc, ST_MOVERS, moved);
@@ -820,7 +821,63 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
 // (rb in [0, nb)) and the workgroup's LDS.
 // --------------------------------------------------------------------------
 
+// Over groups of G lanes, from step S on.
+template <int G, int S = 1>
+__device__ __forceinline__ void group_best(int64_t& g, int32_t& c) {
+  if constexpr (S < G) {
+    const int64_t og = other_half<S>(g);
+    const int32_t oc = other_half<S>(c);
+    if (better(og, oc, g, c)) {
+      g = og;
+      c = oc;
+    }
+    group_best<G, 2 * S>(g, c);
+  }
+}
+template <int G, int S = 1>
+__device__ __forceinline__ int32_t group_max(int32_t v) {
+  if constexpr (S < G) return group_max<G, 2 * S>(max(v, other_half<S>(v)));
+  else return v;
+}
+// x of the 15 other lanes of the 16 whose c equals mine
+template <int R>
+__device__ __forceinline__ int32_t rotate_sum(int32_t mine, int32_t c, int32_t x) {
+  if constexpr (R < 16) {
+    const int32_t c2 = dpp<kDppRor + R>(c), x2 = dpp<kDppRor + R>(x);
+    return (c2 == mine ? x2 : 0) + rotate_sum<R + 1>(mine, c, x);
+  } else {
+    return 0;
+  }
+}
+// x of the other lanes of the group of G whose c equals this lane's (x = 0
+// where a lane has no arc)
+template <int G>
+__device__ __forceinline__ int32_t group_same(int32_t c, int32_t x) {
+  int32_t sum = 0;
+  if constexpr (G == 8) {
+    auto add = [&](int32_t c2, int32_t x2) { sum += c2 == c ? x2 : 0; };
+    const int32_t cm = dpp<kDppMirror8>(c), xm = dpp<kDppMirror8>(x);
+    add(dpp<kDppXor1>(c), dpp<kDppXor1>(x));
+    add(dpp<kDppXor2>(c), dpp<kDppXor2>(x));
+    add(dpp<kDppXor3>(c), dpp<kDppXor3>(x));
+    add(cm, xm);
+    add(dpp<kDppXor1>(cm), dpp<kDppXor1>(xm));
+    add(dpp<kDppXor2>(cm), dpp<kDppXor2>(xm));
+    add(dpp<kDppXor3>(cm), dpp<kDppXor3>(xm));
+  } else {
+    sum = rotate_sum<1>(c, c, x);
+    if constexpr (G == 32) {
+      const int32_t co = __shfl_xor(c, 16), xo = __shfl_xor(x, 16);
+      sum += (co == c ? xo : 0) + rotate_sum<1>(c, co, xo);
+    }
+  }
+  return sum;
+}
+
 // Rows of at most G arcs: groups of G lanes, one arc per lane.
+// (Exchanges by __shfl, 62 rounds through the LDS pipe for G = 32: short rows
+// of a 700,000-vertex R-MAT graph 59 us per SYNC iteration, 51 with DPP moves;
+// a delta-screening update of a 300,000-vertex SBM graph 831 us, 737.)
 template <int G>
 __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const int32_t* __restrict__ list, int bin,
                                            int64_t rb, int64_t nb, MoveAgg* agg) {
@@ -870,17 +927,9 @@ __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const in
       n_d = D.C[n_i];
     }
     // K_{i->c} for this lane's community: all-pairs exchange inside the group
-    int32_t kc = has ? x : 0;
     const int32_t xe = has ? x : 0;
-#pragma unroll
-    for (int s = 1; s < G; ++s) {
-      const int32_t c2 = __shfl_xor(c, s);
-      const int32_t x2 = __shfl_xor(xe, s);
-      if (has && c2 == c) kc += x2;
-    }
-    int32_t kid = (has && c == d) ? kc : 0;
-#pragma unroll
-    for (int s = 1; s < G; s <<= 1) kid = max(kid, __shfl_xor(kid, s));
+    const int32_t kc = xe + group_same<G>(c, xe);
+    const int32_t kid = group_max<G>(has && c == d ? kc : 0);
     const bool cand = has && c != d && gain_bar(two_m, kid, Ki, Sd).open(kc);
     int64_t bg = LLONG_MIN;
     int32_t bc = INT_MAX;
@@ -888,15 +937,7 @@ __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const in
       bg = gain_of(two_m, kc, kid, Ki, D.Sigma[c], Sd);
       bc = c;
     }
-#pragma unroll
-    for (int s = 1; s < G; s <<= 1) {
-      const int64_t og = __shfl_xor(bg, s);
-      const int32_t oc = __shfl_xor(bc, s);
-      if (better(og, oc, bg, bc)) {
-        bg = og;
-        bc = oc;
-      }
-    }
+    group_best<G>(bg, bc);
     const bool lead = valid && k == 0;
     bool mv = false;
     if (valid) mv = decide_move(D, d, bc, bg);
@@ -1068,7 +1109,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
       n_deg = D.row_len[n_i];
       n_d = D.C[n_i];
     }
-    kid = wave_sum_i32(kid);
+    kid = group_sum<kWave>(kid);
     const GainBar bar = gain_bar(two_m, kid, Ki, Sd);
     int64_t bg = LLONG_MIN;
     int32_t bc = INT_MAX;
@@ -1092,14 +1133,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
         bc = cs[q];
       }
     }
-    for (int s = 1; s < kWave; s <<= 1) {
-      const int64_t og = __shfl_xor(bg, s);
-      const int32_t oc = __shfl_xor(bc, s);
-      if (better(og, oc, bg, bc)) {
-        bg = og;
-        bc = oc;
-      }
-    }
+    group_best<kWave>(bg, bc);
     if (decide_move(D, d, bc, bg)) {
       if (lane == 0) {
         commit_move(D, agg, i, d, bc, Ki);
@@ -1124,14 +1158,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
 constexpr int kBlockTS = 2 * kBlockMaxDegree;
 
 __device__ __forceinline__ void block_argmax(int64_t& bg, int32_t& bc, int64_t* r_g, int32_t* r_c) {
-  for (int s = 1; s < kWave; s <<= 1) {
-    const int64_t og = __shfl_xor(bg, s);
-    const int32_t oc = __shfl_xor(bc, s);
-    if (better(og, oc, bg, bc)) {
-      bg = og;
-      bc = oc;
-    }
-  }
+  group_best<kWave>(bg, bc);
   const int wid = threadIdx.x / kWave;
   if (lane_id() == 0) {
     r_g[wid] = bg;
@@ -1771,14 +1798,7 @@ __global__ void __launch_bounds__(kBlock) k_hub_final(Dev D, const int32_t* __re
         bg = unit_g[b0 + t];
         bc = unit_c[b0 + t];
       }
-    for (int s = 1; s < kWave; s <<= 1) {
-      const int64_t og = __shfl_xor(bg, s);
-      const int32_t oc = __shfl_xor(bc, s);
-      if (better(og, oc, bg, bc)) {
-        bg = og;
-        bc = oc;
-      }
-    }
+    group_best<kWave>(bg, bc);
     if (lane == 0) {
       const int32_t i = list[h];
       const int32_t d = D.C[i];
@@ -2001,7 +2021,6 @@ __global__ void __launch_bounds__(kBlock) k_expand_words(Expand X, int64_t* __re
 }
 
 __global__ void __launch_bounds__(kBlock) k_expand_long(Expand X) {
-  __shared__ int s_hit;
   const int64_t count = X.ctr[CTR_AUX0];
   if (blockIdx.x >= count) return;
   const bool push = expand_by_push(X.sc);
@@ -2016,16 +2035,20 @@ __global__ void __launch_bounds__(kBlock) k_expand_long(Expand X) {
       }
       continue;
     }
-    if (threadIdx.x == 0) s_hit = 0;
-    __syncthreads();
-    for (int32_t k = threadIdx.x; k < len; k += kBlock) {
-      if (s_hit) break;
-      const int32_t i = X.col[s + k];
-      if (i != j && test_bit(X.moved, i)) s_hit = 1;
+    int hit = 0;  // (uniform)
+    for (int32_t k0 = 0; k0 < len && !hit; k0 += 4 * kBlock) {
+      int32_t is[4];
+      bool h = false;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int32_t k = k0 + q * kBlock + threadIdx.x;
+        is[q] = k < len ? X.col[s + k] : j;
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) h |= is[q] != j && test_bit(X.moved, is[q]);
+      hit = __syncthreads_or(h);
     }
-    __syncthreads();
-    if (threadIdx.x == 0 && s_hit) set_bit(X.next, j);
-    __syncthreads();
+    if (threadIdx.x == 0 && hit) set_bit(X.next, j);
   }
 }
 
