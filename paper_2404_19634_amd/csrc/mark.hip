@@ -29,7 +29,11 @@ __device__ __forceinline__ bool update_ok(int32_t a, int32_t b, int32_t n) {
   return a >= 0 && b >= 0 && a < n && b < n && a != b;
 }
 
-constexpr int kUwItems = 4;                         // updates per thread
+// Updates per thread: one up to kUwFew updates, where more workgroups shorten
+// the chain (16,000 updates: 16 us with four, 12 with one); beyond, fewer
+// workgroups flush fewer tables into the same totals (50,000: 23, 42).
+constexpr int kUwItemsMany = 4;
+constexpr int64_t kUwFew = 24576;
 constexpr int kUwSlots = 2048;                      // LDS table slots
 constexpr int kUwProbes = 16;
 // With `fr` given, the same pass also does DF's initial marking (both read
@@ -38,6 +42,7 @@ constexpr int kUwProbes = 16;
 // [0, n) or a self-loop (a batch apply_batch would have refused) is skipped
 // and flags LV_EINVAL, so a mismatched batch is reported, never applied out
 // of bounds.
+template <int kUwItems>
 __global__ void __launch_bounds__(kBlock) k_update_weights(const int32_t* __restrict__ du, const int32_t* __restrict__ dv,
                                  const int32_t* __restrict__ dw, int64_t nd, const int32_t* __restrict__ iu,
                                  const int32_t* __restrict__ iv, const int32_t* __restrict__ iw, int64_t ni,
@@ -290,9 +295,11 @@ void launch_update_weights(const lv_edges& del, const lv_edges& ins, int32_t n, 
                            hipStream_t st) {
   const int64_t total = del.count + ins.count;
   if (total == 0) return;
-  const int blocks = static_cast<int>((total + kBlock * kUwItems - 1) / (kBlock * kUwItems));
-  hipLaunchKernelGGL(k_update_weights, dim3(blocks), dim3(kBlock), 0, st, del.u, del.v,
-                     del.w, del.count, ins.u, ins.v, ins.w, ins.count, n, C, K, Sigma, df_frontier, df_list, ctr);
+  const bool few = total <= kUwFew;
+  const int per = kBlock * (few ? 1 : kUwItemsMany);
+  hipLaunchKernelGGL(few ? k_update_weights<1> : k_update_weights<kUwItemsMany>,
+                     dim3(static_cast<unsigned>((total + per - 1) / per)), dim3(kBlock), 0, st, del.u, del.v, del.w,
+                     del.count, ins.u, ins.v, ins.w, ins.count, n, C, K, Sigma, df_frontier, df_list, ctr);
 }
 
 void launch_batch_weight_sums(const lv_edges& del, const lv_edges& ins, int64_t* ctr, hipStream_t st) {

@@ -505,7 +505,7 @@ constexpr int kBinStats = 3 + 2 * NBINS;  // processed, arcs, affected, per-bin 
 // Items (words or listed vertices) per thread per pass: the kernel is a chain
 // of memory round trips, shortest with one item and four times the workgroups
 // (100,000 listed vertices 29 us with four, 21 with two, 17 with one; 32,000:
-// 26, 20, 16).
+// 26, 20, 16; then 15 and 14 with the bins' counts taken from LDS).
 constexpr int kBinPer = 1;
 constexpr int kBinHubs = 2 * kBlock;      // hubs a workgroup reserves together per pass
 
@@ -572,9 +572,9 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
   const bool lm = s_list != 0;
   const int64_t items = lm ? s_rbase[kFlRegions] : words;
   int64_t arcs = 0, processed = 0, affected = 0;
-  int64_t bin_verts[NBINS], bin_arcs[NBINS];
+  int64_t bin_arcs[NBINS];
 #pragma unroll
-  for (int q = 0; q < NBINS; ++q) bin_verts[q] = bin_arcs[q] = 0;
+  for (int q = 0; q < NBINS; ++q) bin_arcs[q] = 0;
   // each thread takes kBinPer items (words or listed vertices) per pass and
   // issues their loads together: a pass costs a few memory round trips,
   // not a few per item.  A listed vertex's degree is read once.
@@ -684,8 +684,6 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
         }
       });
 #pragma unroll
-    for (int q = 0; q < NBINS; ++q) bin_verts[q] += cnt[q];
-#pragma unroll
     for (int q = 0; q < NBINS; ++q)
       if (cnt[q]) atomicAdd(&s_cnt[q], cnt[q]);
     __syncthreads();
@@ -695,6 +693,7 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
                                     reinterpret_cast<unsigned long long*>(&rc[rc_bin(threadIdx.x)]),
                                     static_cast<unsigned long long>(c)))
                               : 0;
+      s_stat[3 + threadIdx.x] += static_cast<unsigned long long>(c);  // (its vertices)
       s_cnt[threadIdx.x] = 0;
     }
     __syncthreads();
@@ -792,20 +791,16 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
   // (skipped by workgroups that met no vertex)
   if (__syncthreads_or(processed != 0 || affected != 0) == 0) return;
   {
-    int64_t v[kBinStats];
-    v[0] = processed;
-    v[1] = arcs;
-    v[2] = affected;
+    auto add = [&](int q, int64_t v) {
+      if (!__any(v != 0)) return;
+      v = group_sum<kWave>(v);
+      if (lane_id() == 0) atomicAdd(&s_stat[q], static_cast<unsigned long long>(v));
+    };
+    add(0, processed);
+    add(1, arcs);
+    add(2, affected);
 #pragma unroll
-    for (int q = 0; q < NBINS; ++q) {
-      v[3 + q] = bin_verts[q];
-      v[3 + NBINS + q] = bin_arcs[q];
-    }
-#pragma unroll
-    for (int q = 0; q < kBinStats; ++q) {
-      const int64_t t = wave_sum_i64(v[q]);
-      if (lane_id() == 0 && t) atomicAdd(&s_stat[q], static_cast<unsigned long long>(t));
-    }
+    for (int q = 0; q < NBINS; ++q) add(3 + NBINS + q, bin_arcs[q]);
   }
   __syncthreads();
   if (threadIdx.x < kBinStats && s_stat[threadIdx.x]) {
