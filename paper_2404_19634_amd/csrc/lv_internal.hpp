@@ -271,6 +271,23 @@ __device__ __forceinline__ T group_sum(T v) {
   else return v;
 }
 
+__device__ __forceinline__ bool better(int64_t g1, int32_t c1, int64_t g0, int32_t c0) {
+  return g1 > g0 || (g1 == g0 && c1 < c0);
+}
+// The best (gain, community) over groups of G lanes, in every lane.
+template <int G, int S = 1>
+__device__ __forceinline__ void group_best(int64_t& g, int32_t& c) {
+  if constexpr (S < G) {
+    const int64_t og = other_half<S>(g);
+    const int32_t oc = other_half<S>(c);
+    if (better(og, oc, g, c)) {
+      g = og;
+      c = oc;
+    }
+    group_best<G, 2 * S>(g, c);
+  }
+}
+
 // Wave-aggregated append: lanes with `pred` get consecutive slots of
 // `list` after atomically bumping *count.  Returns the slot or -1.
 __device__ __forceinline__ int64_t wave_append(bool pred, int64_t* count) {

@@ -49,9 +49,6 @@ __device__ __forceinline__ uint32_t mix64(uint64_t k) {
   return static_cast<uint32_t>(k);
 }
 
-__device__ __forceinline__ bool better(int64_t g1, int32_t c1, int64_t g0, int32_t c0) {
-  return g1 > g0 || (g1 == g0 && c1 < c0);
-}
 
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -490,7 +487,7 @@ struct Many {
       }
     }
     wave_sync();
-    kid = wave_sum_i32(kid);
+    kid = group_sum<kWave>(kid);
     // candidates whose gain bound K_{v->c} (2m - K_v) - tb is not positive
     // (Σ_c >= K_{v->c}) cannot be chosen; their Σ_c is not read
     const int64_t tb = m.two_m * kid - Kv * (Sd - Kv), dm = m.two_m - Kv;
@@ -518,14 +515,7 @@ struct Many {
         bc = cs[q];
       }
     }
-    for (int sft = 1; sft < kWave; sft <<= 1) {
-      const int64_t og = __shfl_xor(bg, sft);
-      const int32_t oc = __shfl_xor(bc, sft);
-      if (better(og, oc, bg, bc)) {
-        bg = og;
-        bc = oc;
-      }
-    }
+    if (__any(bc != INT_MAX)) group_best<kWave>(bg, bc);
     wave_sync();  // the table is reused by the wavefront's next vertex
     const bool mv = decide(it, m, d, bc, bg);
     if (m.mode == LV_SYNC) {

@@ -116,9 +116,6 @@ __device__ __forceinline__ int64_t load_two_m(const Dev& D) {
   return (t > 0 && t < kTwoMLimit) ? t : 0;
 }
 
-__device__ __forceinline__ bool better(int64_t g1, int32_t c1, int64_t g0, int32_t c0) {
-  return g1 > g0 || (g1 == g0 && c1 < c0);
-}
 
 __device__ __forceinline__ int64_t gain_of(int64_t two_m, int64_t kic, int64_t kid, int64_t Ki, int64_t Sc,
                                            int64_t Sd) {
@@ -818,18 +815,6 @@ __global__ void __launch_bounds__(kBlock) k_bin_frontier(uint32_t* __restrict__ 
 
 // Over groups of G lanes, from step S on.
 template <int G, int S = 1>
-__device__ __forceinline__ void group_best(int64_t& g, int32_t& c) {
-  if constexpr (S < G) {
-    const int64_t og = other_half<S>(g);
-    const int32_t oc = other_half<S>(c);
-    if (better(og, oc, g, c)) {
-      g = og;
-      c = oc;
-    }
-    group_best<G, 2 * S>(g, c);
-  }
-}
-template <int G, int S = 1>
 __device__ __forceinline__ int32_t group_max(int32_t v) {
   if constexpr (S < G) return group_max<G, 2 * S>(max(v, other_half<S>(v)));
   else return v;
@@ -932,7 +917,7 @@ __device__ __forceinline__ void role_small(const Dev& D, int64_t two_m, const in
       bg = gain_of(two_m, kc, kid, Ki, D.Sigma[c], Sd);
       bc = c;
     }
-    group_best<G>(bg, bc);
+    if (__any(cand)) group_best<G>(bg, bc);
     const bool lead = valid && k == 0;
     bool mv = false;
     if (valid) mv = decide_move(D, d, bc, bg);
@@ -1128,7 +1113,7 @@ __device__ __forceinline__ void role_wave(const Dev& D, int64_t two_m, const int
         bc = cs[q];
       }
     }
-    group_best<kWave>(bg, bc);
+    if (__any(bc != INT_MAX)) group_best<kWave>(bg, bc);
     if (decide_move(D, d, bc, bg)) {
       if (lane == 0) {
         commit_move(D, agg, i, d, bc, Ki);
