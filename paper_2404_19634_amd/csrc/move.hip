@@ -24,18 +24,20 @@
 // Arcs into the vertex's own community d are summed in registers in every
 // tier, which keeps the most frequent key out of the hashtable atomics.
 //
-// A sub-round is binning, then (with hub rows) a hub table clear, the scan,
-// then (with hub rows) hub partial argmaxes, decisions and expansion.  For small
-// frontiers the scan is one fused kernel whose workgroups take the roles
-// of the per-bin kernels (the block ranges of the roles laid end to end in
-// one grid): such launches are bound by launch latency, so the count
-// matters.  Large frontiers run the same kernel once per bin, in order of
-// degree, so that ASYNC moves of one bin are seen by the next.
+// A sub-round is binning (or its part of the iteration's plan, plan.hip),
+// then (with hub rows) a hub table clear, the scan, then (with hub rows) hub
+// partial argmaxes, decisions and expansion.  For small frontiers the scan is
+// one fused kernel whose workgroups take the roles of the per-bin kernels (the
+// block ranges of the roles laid end to end in one grid): such launches are
+// bound by their chains of loads and by launch latency, so the count matters.
+// Larger frontiers run the same kernel once per bin, in order of degree, so
+// that ASYNC moves of one bin are seen by the next; bins of short rows share
+// a launch where that costs no modularity (launch_scan).
 //
 // SYNC mode reads the iteration-start state and records movers; a separate
 // kernel applies them.  ASYNC mode applies each move's membership at once.
 // Both expand the next frontier from the kernel that holds the mover's arcs
-// (or leave it to the pull kernels when the frontier is large).
+// (or leave it to the k_expand_* kernels when the frontier is large).
 #include <climits>
 
 #include <hip/hip_ext.h>
