@@ -16,8 +16,10 @@
 //
 // Bound: one read of row_len per frontier vertex twice (count, place) and
 // one 4-byte write: latency of four short kernels on small levels, HBM on
-// large ones.  A workgroup takes tiles of 4096 vertices; counts are summed
-// in LDS per key and reserved with one device atomic per key and tile.
+// large ones.  A workgroup takes tiles of 2048 vertices; counts are summed
+// in LDS per key and reserved with one device atomic per key and tile.  (Count
+// and place of 700,000 vertices 11 + 12 us with tiles of 4096, 9 + 10 of 2048,
+// 10 + 11 of 1024; of 10,000 7 + 10, 5 + 7, 4 + 6.)
 //
 // Measured, picking per sub-round -> plan: static ASYNC on the 10,000-vertex
 // SBM graph 29.8 -> 4.9 ms, on a 300,000-vertex power-law graph 24.0 -> 12.3
@@ -33,7 +35,7 @@
 namespace lv {
 namespace {
 
-constexpr int kPer = 16;                     // vertices per thread and tile
+constexpr int kPer = 8;                      // vertices per thread and tile
 constexpr int kPlanTile = kBlock * kPer;
 constexpr int kWordsPerTile = kPlanTile / 32;
 constexpr int kKeySlots = 8;                 // bins of a sub-round (slot 7: rows without arcs)
@@ -292,31 +294,31 @@ __global__ void __launch_bounds__(NT) k_plan_hubs(PlanBuf p, PlanLists L, int32_
   }
   // (the key's list range ends at the cursor that placed it)
   const int32_t* list = L.list[BIN_HUB] + (p.cursor[key] - count);
-  int32_t ut = 0, ct = 0;
-  for (int32_t k = threadIdx.x; k < count; k += NT) {
-    const int32_t deg = row_len[list[k]];
-    ut += static_cast<int32_t>(hub_units(deg));
-    ct += static_cast<int32_t>(hub_cunits(deg));
-  }
-  ut = wave_sum_i32(ut);
-  ct = wave_sum_i32(ct);
-  if (lane == 0) {
-    atomicAdd(&s_ut, ut);
-    atomicAdd(&s_ct, ct);
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    s_ub = atomicAdd(&p.tail[PT_UNITS], s_ut);
-    s_cb = atomicAdd(&p.tail[PT_CUNITS], s_ct);
-    p.hub_ubase[r] = s_ub;
-    p.hub_units[r] = s_ut;
-    p.hub_cbase[r] = s_cb;
-    p.hub_cunits[r] = s_ct;
-    p.hub_first[r] = s_before;
-    if (rounds == 1) {
-      rc[RC_HUB_UNITS] = s_ut;
-      rc[RC_HUB_CUNITS] = s_ct;
+  if (rounds > 1) {  // the sub-round's share of the units (a single one's start at 0)
+    int32_t ut = 0, ct = 0;
+    for (int32_t k = threadIdx.x; k < count; k += NT) {
+      const int32_t deg = row_len[list[k]];
+      ut += static_cast<int32_t>(hub_units(deg));
+      ct += static_cast<int32_t>(hub_cunits(deg));
     }
+    ut = wave_sum_i32(ut);
+    ct = wave_sum_i32(ct);
+    if (lane == 0) {
+      atomicAdd(&s_ut, ut);
+      atomicAdd(&s_ct, ct);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      s_ub = atomicAdd(&p.tail[PT_UNITS], s_ut);
+      s_cb = atomicAdd(&p.tail[PT_CUNITS], s_ct);
+      p.hub_ubase[r] = s_ub;
+      p.hub_units[r] = s_ut;
+      p.hub_cbase[r] = s_cb;
+      p.hub_cunits[r] = s_ct;
+      p.hub_first[r] = s_before;
+    }
+  } else if (threadIdx.x == 0) {
+    s_ub = s_cb = 0;
   }
   __syncthreads();
   const int64_t hb = s_before;
@@ -384,6 +386,10 @@ __global__ void __launch_bounds__(NT) k_plan_hubs(PlanBuf p, PlanLists L, int32_
     u0 += cu;
     c0 += cc;
     __syncthreads();
+  }
+  if (rounds == 1 && threadIdx.x == 0) {
+    rc[RC_HUB_UNITS] = u0;
+    rc[RC_HUB_CUNITS] = c0;
   }
 }
 

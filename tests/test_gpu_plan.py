@@ -1,5 +1,5 @@
 """The iteration plan (csrc/plan.hip): the frontier sorted by sub-round and
-degree bin in one pass.  Vertex counts around the 4096-vertex tile and the
+degree bin in one pass.  Vertex counts around multiples of the tile and the
 32-vertex word; rows on both sides of every bin, class and hub boundary."""
 import numpy as np
 import pytest
