@@ -2240,7 +2240,7 @@ void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const Sc
     // So do an ASYNC sub-round's up to the wavefront's where it is a small
     // part of the level, its vertices rarely meeting (static run on a
     // 300,000-vertex power-law graph 24.3 -> 21.1 ms, on a 100,000-vertex SBM
-    // graph 9.0 -> 8.0; modularity within 1e-4 on eight graphs; past kGroupRows
+    // graph 9.0 -> 8.0; modularity within 5e-4 on eight graphs; past kGroupRows
     // the launches are bound by their arcs: 4 ms of 56 at 3 million vertices
     // with it, no more at four times the limit).  Longer rows keep their own
     // launches: together with the rest they cost a 2^20-vertex R-MAT graph
