@@ -419,12 +419,12 @@ struct Many {
     }
   }
 
-  // A vertex, its row, and this lane's first arc of it with its community.
+  // A vertex, its row, and this lane's first arc of it.
   static constexpr int kArcs = kManyWaveDeg / kWave;
   struct Row {
     int64_t rs = 0;
     int32_t v = 0, deg = 0, d = 0;
-    int32_t j = 0, x = 0, c = 0;
+    int32_t j = 0, x = 0;
   };
   static __device__ __forceinline__ void row_meta(const ManyItem& it, int32_t v, Row& r) {
     r.v = v;
@@ -455,7 +455,6 @@ struct Many {
     int32_t js[U], xs[U], cs[U], own[U];
     js[0] = r.j;
     xs[0] = r.x;
-    cs[0] = r.c;
 #pragma unroll
     for (int q = 1; q < U; ++q) {
       if (q >= nu) continue;
@@ -464,7 +463,7 @@ struct Many {
       xs[q] = k < deg ? it.w[r.rs + k] : 0;
     }
 #pragma unroll
-    for (int q = 1; q < U; ++q)
+    for (int q = 0; q < U; ++q)
       if (q < nu) cs[q] = js[q] != v ? it.C[js[q]] : d;
     int32_t kid = 0;
 #pragma unroll
@@ -671,8 +670,11 @@ __global__ void __launch_bounds__(NT) k_many_df(const int32_t* __restrict__ coun
         }
       wave_sync();
       // A burst touches each graph once, so these are cold misses: while a
-      // vertex is scanned, the communities of the next one's arcs, the arcs
-      // of the one after it and the bounds of the third are on their way.
+      // vertex is scanned, the arcs of the next two and the bounds of the
+      // third are on their way.  The communities of a vertex's arcs are not:
+      // they are gathered, all together, once the vertex before it has moved,
+      // so that an ASYNC decision sees the wavefront's own last move and no
+      // mixture of older and newer memberships.
       typename M::Row r0, r1, r2;
       auto listed = [&](int32_t q) { return s.list[min(q, nsmall - 1)]; };
       if (wv < nsmall) {
@@ -681,11 +683,9 @@ __global__ void __launch_bounds__(NT) k_many_df(const int32_t* __restrict__ coun
         M::row_meta(it, listed(wv + 2 * kNW), r2);
         M::row_arc(it, r0);
         M::row_arc(it, r1);
-        r0.c = it.C[r0.j];
       }
       for (int32_t q = wv; q < nsmall; q += kNW) {
         const typename M::Row now = r0;
-        r1.c = it.C[r1.j];
         r0 = r1;
         r1 = r2;
         M::row_arc(it, r1);

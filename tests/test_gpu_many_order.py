@@ -1,0 +1,57 @@
+"""ASYNC order inside the batched launch: a wavefront decides a vertex on the
+memberships its own last move left."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2404_19634_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _follow(waves):
+    """Per wavefront w the vertices a = w, b = waves + w (which it visits one
+    after the other), x and y, each a community of its own; arcs a-x of weight
+    6 and b-y of 3, and a batch that adds a-b of 5, so that exactly the a and b
+    are in the frontier, in one word of it.  a joins x; b then has 5 into x's
+    community (through a) and 3 into y's, and must follow a there.  Seen in its
+    old community, which is empty now, a would be the better choice:
+    2m 5 > 2m 5 - K_b (K_x + K_a)."""
+    w = np.arange(waves)
+    a, b, x, y = (w + k * waves for k in range(4))
+    e = W.Edges(4 * waves, np.concatenate([a, b]).astype(np.int32), np.concatenate([x, y]).astype(np.int32),
+                np.repeat([6, 3], waves).astype(np.int32))
+    return e, (a, b, np.full(waves, 5)), (a, b, x, y)
+
+
+@pytest.mark.parametrize("count,waves", [(3, 16), (512, 16), (513, 4)])  # 1024 threads a graph, or 256
+def test_async_sees_its_own_last_move(count, waves):
+    from paper_2404_19634_amd import lib
+    e, ins, (a, b, x, y) = _follow(waves)
+    n = e.n
+    k0 = np.bincount(e.u, weights=e.w, minlength=n) + np.bincount(e.v, weights=e.w, minlength=n)
+    none = lib.Edges([], [], [])
+    gs, states, bs, scratch = [], [], [], []
+    for _ in range(count):
+        gs.append(lib.Graph.from_edges(e, slack_frac=1.0, slack_min=8))
+        st = lib.State.from_host(np.arange(n, dtype=np.int32), k0.astype(np.int64), k0.astype(np.int64))
+        st.size = torch.ones(n, dtype=torch.int32, device="cuda")
+        states.append(st)
+        bs.append(lib.Batch(none, lib.Edges(*ins)))
+        scratch.append(lib.many_scratch(n, 32))
+    ws = torch.empty(int(lib.load().lv_workspace_bytes(gs[0].n, gs[0].cap)), dtype=torch.uint8, device="cuda")
+    status, stats = lib.louvain_df_many(gs, bs, states, scratch, 32, ws=ws, mode="async", swap_guard=0,
+                                        max_iterations=1, max_passes=1)
+    assert status == [0] * count
+    want = np.arange(n, dtype=np.int32)
+    want[a] = want[b] = x
+    K = k0.copy()
+    K[a] += 5
+    K[b] += 5
+    for k, st in enumerate(states):
+        C, Kg, S = st.host()
+        assert np.array_equal(C, want), k
+        assert np.array_equal(Kg, K) and np.array_equal(S, np.bincount(want, weights=K, minlength=n)), k
+        assert stats[k]["moves"] == 2 * waves and stats[k]["vertices_affected"] == 2 * waves, k
+        gain = 6 * 28 * waves - 11 * 6 + 5 * 28 * waves - 8 * (6 + 11)
+        assert stats[k]["iter_gain"][0][0] == waves * gain, k
