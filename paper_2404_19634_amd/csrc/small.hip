@@ -425,10 +425,12 @@ __global__ void __launch_bounds__(kSB) k_small_tail(Upd<int32_t> U, int32_t edit
     } s;
     struct {
       int32_t pos[2 * kSmallUpdates], deg[2 * kSmallUpdates];
+      int32_t u[2 * kSmallUpdates], c[2 * kSmallUpdates];  // inclusive sums of the hubs' units
     } h;
   };
   __shared__ Lds L;
   __shared__ int32_t s_err, s_nh;
+  __shared__ int64_t s_scan[kSW];
   __shared__ int32_t s_bin[NBINS];
   __shared__ unsigned long long s_arc[NBINS];
   __shared__ int32_t s_proc;
@@ -536,26 +538,58 @@ __global__ void __launch_bounds__(kSB) k_small_tail(Upd<int32_t> U, int32_t edit
   __syncthreads();
   int64_t* rc = ctr + CTR_ROUND0;
   const int nh = s_nh;
-  int64_t off = 0, u0 = 0, c0 = 0;
-  for (int k = 0; k < nh; ++k) {  // hubs one after another, each hub's units by all threads
-    const int32_t p = L.h.pos[k], d = L.h.deg[k];
-    if (t == 0) {
-      df.hub.off[p] = off;
-      df.hub.cbase[p] = c0;
-      df.hub.cnum[p] = static_cast<int32_t>(hub_cunits(d));
-      df.hub_kid[p] = 0;
+  int32_t u0 = 0, c0 = 0;
+  if (nh > 0) {
+    // Two hubs to a thread: prefix sums give each its pool slots and units,
+    // and a unit finds its hub by a search of the sums.  (Hubs one after
+    // another an update of 300 edges between 512 rows of 2600 arcs took 251 us,
+    // of 1024 between 2048 rows 725; the grid-wide kernels 200 and 347; this
+    // 118 and 240.)
+    int64_t slots = 0, units = 0;  // units | clear units << 32 (each sum stays under 2^31)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (2 * t + q < nh) {
+        const int32_t d = L.h.deg[2 * t + q];
+        slots += hub_slots(d);
+        units += (hub_cunits(d) << 32) | hub_units(d);
+      }
+    int64_t all_slots = 0, all_units = 0;
+    int64_t off = scan_1024(slots, &all_slots, s_scan);
+    int64_t at_unit = scan_1024(units, &all_units, s_scan);
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+      if (2 * t + q < nh) {
+        const int32_t p = L.h.pos[2 * t + q], d = L.h.deg[2 * t + q];
+        df.hub.off[p] = off;
+        df.hub.cbase[p] = at_unit >> 32;
+        df.hub.cnum[p] = static_cast<int32_t>(hub_cunits(d));
+        df.hub_kid[p] = 0;
+        off += hub_slots(d);
+        at_unit += (hub_cunits(d) << 32) | hub_units(d);
+        L.h.u[2 * t + q] = static_cast<int32_t>(at_unit);
+        L.h.c[2 * t + q] = static_cast<int32_t>(at_unit >> 32);
+      }
+    __syncthreads();
+    auto owner = [&](const int32_t* incl, int32_t x) {  // the first hub whose inclusive sum exceeds x
+      int lo = 0, hi = nh - 1;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (incl[mid] > x) hi = mid; else lo = mid + 1;
+      }
+      return lo;
+    };
+    u0 = static_cast<int32_t>(all_units);
+    c0 = static_cast<int32_t>(all_units >> 32);
+    for (int32_t x = t; x < u0; x += kSB) {
+      const int k = owner(L.h.u, x);
+      df.hub.u_b[x] = L.h.pos[k];
+      df.hub.u_a[x] = static_cast<int64_t>(x - (k ? L.h.u[k - 1] : 0)) * kHubUnitArcs;
     }
-    for (int64_t u = t; u < hub_units(d); u += kSB) {
-      df.hub.u_b[u0 + u] = p;
-      df.hub.u_a[u0 + u] = u * kHubUnitArcs;
+    for (int32_t x = t; x < c0; x += kSB) {
+      const int k = owner(L.h.c, x);
+      df.hub.c_b[x] = L.h.pos[k];
+      df.hub.c_s[x] = static_cast<int64_t>(x - (k ? L.h.c[k - 1] : 0)) * kHubClearSlots;
     }
-    for (int64_t u = t; u < hub_cunits(d); u += kSB) {
-      df.hub.c_b[c0 + u] = p;
-      df.hub.c_s[c0 + u] = u * kHubClearSlots;
-    }
-    off += hub_slots(d);
-    u0 += hub_units(d);
-    c0 += hub_cunits(d);
   }
   int64_t* sc = ctr + CTR_STATS0;
   if (t < NBINS) {
