@@ -37,7 +37,7 @@ PROFILES = os.path.join(ROOT, "profiles")
 # and, per active vertex, its row length and one list entry (4 + 4 B).  A
 # hub row's decision units read at most one 8 B (community, weight) pair
 # per arc; the clear kernel resets per-hub sums (and the global tables of
-# rows above 2^18 arcs, not priced here).
+# rows above 2^20 arcs, not priced here).
 SCAN_BYTES_PER_ARC = 12
 SCAN_BYTES_PER_VERTEX = 24
 BIN_BYTES_PER_WORD = 4
@@ -94,10 +94,13 @@ class KernelMeter:
             self.ms[k] += s["timed_ms"][k]
         arcs, verts = s["bin_arcs"], s["bin_vertices"]
         self.bytes[L.TIME_SCAN] += SCAN_BYTES_PER_ARC * sum(arcs) + SCAN_BYTES_PER_VERTEX * sum(verts)
-        # binning runs once per sub-round; its launches are known when timed
-        words = (self.n + 31) // 32
-        nbin = s["timed_launches"][L.TIME_BINNING]
-        self.bytes[L.TIME_BINNING] += BIN_BYTES_PER_WORD * words * nbin + BIN_BYTES_PER_VERTEX * sum(verts)
+        # an iteration has to read the frontier's words once, however many
+        # sub-rounds the launches counted as binning serve
+        level = self.n
+        for k, its in enumerate(s["iterations"]):
+            self.bytes[L.TIME_BINNING] += BIN_BYTES_PER_WORD * ((level + 31) // 32) * its
+            level = s["communities"][k]
+        self.bytes[L.TIME_BINNING] += BIN_BYTES_PER_VERTEX * sum(verts)
         hub_arcs = arcs[L.BINS.index("hub")]
         self.bytes[L.TIME_HUB_DECIDE] += HUB_PAIR_BYTES_PER_ARC * hub_arcs
 

@@ -122,9 +122,10 @@ typedef struct {
  * up to 2048 arcs (one workgroup, LDS table), and longer hub rows (several
  * workgroups, global table). */
 enum { LV_BIN_G4 = 0, LV_BIN_G8, LV_BIN_G16, LV_BIN_G32, LV_BIN_WAVE, LV_BIN_BLOCK, LV_BIN_HUB, LV_NBINS };
-/* Kernels the measurement hook can time: the fused local-moving scan (all
- * degree bins and the hub-row inserts of a sub-round in one launch), the
- * frontier binning, and the hub-row table clear and decision kernels. */
+/* Kernels the measurement hook can time: the local-moving scan (all degree
+ * bins and the hub-row inserts of a sub-round in one launch, or a launch per
+ * bin), the frontier binning, the hub-row table clear (launched where a row
+ * may keep a global table) and the hub-row decision kernel. */
 enum { LV_TIME_SCAN = 0, LV_TIME_BINNING, LV_TIME_HUB_CLEAR, LV_TIME_HUB_DECIDE, LV_NTIMED };
 
 /* Per-run statistics.  The first block matches the oracle's layout. */
@@ -152,8 +153,10 @@ typedef struct {
   int32_t bin_launches[LV_NBINS];
   /* Launches bracketed by timing events (lv_set_timing) and their summed
    * GPU time, per timed kernel (index LV_TIME_*); zero for kernels that are
-   * not timed.  A launch that bins the frontier, or prepares the hub rows,
-   * of several sub-rounds at once counts as one per sub-round. */
+   * not timed.  Where the frontier of an iteration is sorted for all its
+   * sub-rounds at once, binning counts one per sub-round with vertices, and
+   * its time runs from the begin of the first of those kernels (the ones that
+   * lay out the hub rows included) to the end of the last. */
   int32_t timed_launches[LV_NTIMED];
   double timed_ms[LV_NTIMED];
 } lv_stats;

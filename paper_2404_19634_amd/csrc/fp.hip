@@ -1334,8 +1334,7 @@ lv_status planned_rounds_f(FMove& M, const FWs& w, uint32_t* cur, uint32_t* ever
   a.wave_max = kFWaveMax;
   for (int b = 0; b < NBINS; ++b) a.list[b] = w.list[FB_WAVE];
   a.mem = w.pkeys;  // (read back before the first scan uses the pool)
-  TimerPair none;
-  launch_plan(a, pk, &none, &none, st);
+  launch_plan(a, pk, TimerPair(), st);
   int64_t* host;
   if (lv_status s = lv_pinned_host(&host)) return s;
   F_HIP(hipMemcpyAsync(host, w.pkeys, kPlanArcs + 8 * kPlanKeys, hipMemcpyDeviceToHost, st));

@@ -95,10 +95,6 @@ thread_local Timer g_timer;
 
 }  // namespace
 
-// (a timed run launches the clear even where no row can need it, so that the
-// hook reports it)
-bool timing_hub_clear() { return !g_no_alloc && ((g_timed_mask.load() >> LV_TIME_HUB_CLEAR) & 1u); }
-
 TimerPair timer_pair(int kernel) {
   TimerPair p;
   if (g_no_alloc || !((g_timed_mask.load(std::memory_order_relaxed) >> kernel) & 1u)) return p;
@@ -129,7 +125,7 @@ void timer_collect(int32_t* launches, double* ms) {
   Timer& t = g_timer;
   for (int k = 0; k < t.used; ++k) {
     float x = 0.f;
-    if (t.weight[k] && hipEventElapsedTime(&x, t.ev[2 * k], t.ev[2 * k + 1]) == hipSuccess) {
+    if (hipEventElapsedTime(&x, t.ev[2 * k], t.ev[2 * k + 1]) == hipSuccess) {
       launches[t.kernel[k]] += t.weight[k];
       ms[t.kernel[k]] += x;
     }
@@ -462,8 +458,7 @@ float ms_between(hipEvent_t* ev, int a, int b) {
 lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const std::vector<SubRound>& plan,
                          int64_t* host, lv_stats& S, hipStream_t st) {
   const PlanKeys pk = lv_plan_keys(plan, tu);
-  TimerPair tb = timer_pair(LV_TIME_BINNING), th;
-  if (plan.size() > 1) th = timer_pair(LV_TIME_HUB_CLEAR);  // (a single round's clear is its own launch)
+  const TimerPair tb = timer_pair(LV_TIME_BINNING);
   PlanArgs pa{};
   pa.cur = const_cast<uint32_t*>(a.cur);
   pa.range = a.range;
@@ -484,7 +479,7 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
   pa.stamp = a.stamp;
   pa.hub = HubOut{ws.hub_off, ws.hub_cbase, ws.hub_cnum, ws.u_ins_b, ws.u_ins_a, ws.u_emit_b, ws.u_emit_s};
   pa.hub_kid = ws.hub_kid;
-  launch_plan(pa, pk, &tb, &th, st);
+  launch_plan(pa, pk, tb, st);
   ScanLists L = single_round(ws, true, true);
   if (plan.size() == 1) {
     for (int b = 0; b < NBINS; ++b) S.bin_launches[b] += 1;
@@ -503,7 +498,7 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
   const int32_t *ub = h + kPlanKeys, *un = ub + kPlanRounds, *cb = un + kPlanRounds, *cn = cb + kPlanRounds,
                 *hf = cn + kPlanRounds, *tail = hf + kPlanRounds;
   L.clear = tail[PT_MAXDEG] > kHubPartMaxDeg;
-  int served = 0, hub_rounds = 0;
+  int served = 0;
   for (const SubRound& r : plan) {
     uint32_t mask = 0;
     for (int b = 0; b < NBINS; ++b) {
@@ -516,7 +511,6 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
     if (!mask) continue;
     const bool hubs = mask & (1u << BIN_HUB);
     ++served;
-    hub_rounds += hubs ? 1 : 0;
     L.units = hubs ? un[r.key] : 0;
     L.cunits = hubs ? cn[r.key] : 0;
     L.ubase = hubs ? ub[r.key] : 0;
@@ -525,7 +519,6 @@ lv_status planned_rounds(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, 
     launch_scan(a, ws, tu, L, mask, st);
   }
   timer_weight(tb, std::max(1, served));
-  timer_weight(th, L.clear ? 0 : hub_rounds);
   return LV_OK;
 }
 
@@ -723,7 +716,7 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
         a.clear_cur = r + 1 == plan.size() ? 1 : 0;
         const uint32_t mask = bins_for_degrees(plan[r].deg_lo, plan[r].deg_hi, a.wave_max);
         if (in_bins)  // (rows of over 2^20 arcs keep a table that has to be cleared)
-          launch_scan(a, ws, tu, single_round(ws, g->cap > kHubPartMaxDeg || timing_hub_clear(), !late_expand), mask, st);
+          launch_scan(a, ws, tu, single_round(ws, g->cap > kHubPartMaxDeg, !late_expand), mask, st);
         else
           launch_round(a, ws, tu, plan[r], mask, !late_expand, st);
         for (int b = 0; b < NBINS; ++b) S.bin_launches[b] += (mask >> b) & 1u;

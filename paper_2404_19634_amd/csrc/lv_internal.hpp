@@ -704,7 +704,7 @@ struct PlanArgs {
   int64_t* hub_kid;  // null: no hub units
 };
 struct TimerPair;
-void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* binning, TimerPair* hubs, hipStream_t st);
+void launch_plan(const PlanArgs& a, const PlanKeys& pk, const TimerPair& timer, hipStream_t st);
 // The scans of one sub-round whose lists a plan has made.
 struct ScanLists {
   int32_t* list[NBINS];
@@ -729,7 +729,8 @@ struct TimerPair {
   hipEvent_t stop = nullptr;
   int id = -1;
 };
-// The launch of a pair served `launches` sub-rounds (0: it is not reported).
+// The pair stands for `launches` launches in the report (a plan: one per
+// sub-round that it served).
 void timer_weight(const TimerPair& p, int launches);
 TimerPair timer_pair(int kernel);
 void timer_collect(int32_t* launches, double* ms);  // adds per kernel, resets

@@ -409,26 +409,28 @@ PlanBuf plan_buf(void* mem) {
   return p;
 }
 
-void launch_plan(const PlanArgs& a, const PlanKeys& pk, TimerPair* tb, TimerPair* th, hipStream_t st) {
+void launch_plan(const PlanArgs& a, const PlanKeys& pk, const TimerPair& t, hipStream_t st) {
   const PlanBuf p = plan_buf(a.mem);
   const Frontier f{a.cur, a.range, a.row_len, a.n, a.wave_max};
   PlanLists L;
   for (int b = 0; b < NBINS; ++b) L.list[b] = pk.rounds == 1 ? a.list[b] : a.list[0];
   const int64_t tiles = (static_cast<int64_t>(a.n) + kPlanTile - 1) / kPlanTile;
   const unsigned grid = static_cast<unsigned>(std::max<int64_t>(1, std::min<int64_t>(tiles, 2048)));
-  hipLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, p, a.rc_next, a.sc_next, a.next_cnt,
-                     a.stamp);
+  // (timed from the first kernel's begin to the last one's end)
+  const hipEvent_t none = nullptr;
+  hipExtLaunchKernelGGL(k_plan_begin, dim3(1), dim3(1024), 0, st, t.start, none, 0, p, a.rc_next, a.sc_next,
+                        a.next_cnt, a.stamp);
   hipLaunchKernelGGL(k_plan_count, dim3(grid), dim3(kBlock), 0, st, f, pk, p);
   hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(kBlock), 0, st, pk, p, a.rc, a.sc);
-  hipExtLaunchKernelGGL(k_plan_fill, dim3(grid), dim3(kBlock), 0, st, tb->start, tb->stop, 0, f, pk, p, L, a.ever,
-                        a.sc);
+  hipExtLaunchKernelGGL(k_plan_fill, dim3(grid), dim3(kBlock), 0, st, none, a.hub_kid ? none : t.stop, 0, f, pk, p, L,
+                        a.ever, a.sc);
   if (!a.hub_kid) return;
   if (pk.rounds == 1)
-    hipExtLaunchKernelGGL(k_plan_hubs<1024>, dim3(1), dim3(1024), 0, st, th->start, th->stop, 0, p, L, pk.rounds,
-                          a.row_len, a.hub, a.hub_kid, a.rc);
+    hipExtLaunchKernelGGL(k_plan_hubs<1024>, dim3(1), dim3(1024), 0, st, none, t.stop, 0, p, L, pk.rounds, a.row_len,
+                          a.hub, a.hub_kid, a.rc);
   else
-    hipExtLaunchKernelGGL(k_plan_hubs<kBlock>, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, th->start,
-                          th->stop, 0, p, L, pk.rounds, a.row_len, a.hub, a.hub_kid, a.rc);
+    hipExtLaunchKernelGGL(k_plan_hubs<kBlock>, dim3(static_cast<unsigned>(pk.rounds)), dim3(kBlock), 0, st, none,
+                          t.stop, 0, p, L, pk.rounds, a.row_len, a.hub, a.hub_kid, a.rc);
 }
 
 }  // namespace lv
