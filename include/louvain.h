@@ -176,7 +176,11 @@ typedef struct {
                                 2: degree classes (highest first), hashed within a class */
   int32_t fuse_max_frontier; /* a sub-round scans all degree bins in one launch when its frontier
                                 bound is at most this and an eighth of the level's vertices at
-                                most (else one launch per bin); -1: never */
+                                most.  Else the bins have a launch each, except that short rows
+                                share one: LV_SYNC bins of up to 32 arcs, and the bins up to the
+                                wavefront threshold of an LV_ASYNC sub-round that has at most
+                                16384 such rows, this many and an eighth of the level's vertices.
+                                0 or -1: one launch per bin always */
   int32_t defer_totals;      /* LV_ASYNC: 1 sums a workgroup's Sigma/size changes in LDS and applies
                                 them when it ends; 0 applies each move's changes at once */
   int32_t revisit_min_degree; /* LV_ASYNC, degree-class order: each iteration visits the degree classes

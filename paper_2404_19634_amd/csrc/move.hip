@@ -2238,17 +2238,23 @@ void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const Sc
     // 16 + 14 + 15 + 25 us apart, 59 us together; the workgroup and hub roles
     // 61 + 31 us apart, 111 us together, each with half of the device.)
     // So do an ASYNC sub-round's up to the wavefront's where it is a small
-    // part of the level, its vertices rarely meeting (static run on a
-    // 300,000-vertex power-law graph 24.3 -> 21.1 ms, on a 100,000-vertex SBM
-    // graph 9.0 -> 8.0; modularity within 5e-4 on eight graphs; past kGroupRows
-    // the launches are bound by their arcs: 4 ms of 56 at 3 million vertices
-    // with it, no more at four times the limit).  Longer rows keep their own
-    // launches: together with the rest they cost a 2^20-vertex R-MAT graph
-    // 0.0023 of a modularity of 0.0742.
+    // part of the level, its vertices rarely meeting (static runs, a launch
+    // per bin -> shared: 300,000-vertex Chung-Lu graph 22.9 -> 20.0 ms,
+    // 100,000-vertex SBM graph 8.4 -> 7.2, 2^14-vertex R-MAT graph 5.5 -> 3.6;
+    // past kGroupRows the launches are bound by their arcs: 4 ms of 56 at 3
+    // million vertices with it, no more at four times the limit).  The bins
+    // then do not see each other's moves of the sub-round.  The modularity of
+    // a single graph moves either way (by up to 2% at 3000 vertices), its mean
+    // over 16 or 32 graphs of each of ten kinds (R-MAT 2^10 to 2^16, Chung-Lu
+    // 3000 to 60,000, SBM 4000 and 20,000 vertices) by -0.09% to +0.11%, within
+    // three standard errors but for R-MAT 2^16 (-0.04%).  Longer rows keep
+    // their own launches: together with the rest they cost a 2^20-vertex R-MAT
+    // graph 0.0023 of a modularity of 0.0742.  With fuse_max_frontier 0 or -1
+    // nothing is shared.
     int64_t rows = 0;
     for (int k = 0; k <= BIN_WAVE; ++k) rows += std::max<int64_t>(S.cnt[k], 0);
     const bool part = a.mode != LV_SYNC && S.cnt[0] >= 0 && rows * 8 <= a.g.n;
-    if (part && rows <= kGroupRows) {
+    if (part && rows <= std::min<int64_t>(kGroupRows, tu.fuse_max_frontier)) {
       if (ts <= 128)
         launch_group<128, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
       else if (ts <= 256)
@@ -2258,7 +2264,7 @@ void launch_scan(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const Sc
       else
         launch_group<1024, kShortRoles>(bin_mask, BIN_WAVE, D, b, H, lw, per, st);
       bin_mask &= ~((2u << BIN_WAVE) - 1u);
-    } else if (a.mode == LV_SYNC) {
+    } else if (a.mode == LV_SYNC && tu.fuse_max_frontier > 0) {
       launch_group<128, kSmallRoles>(bin_mask, BIN_G32, D, b, H, sizeof(MoveAgg), per, st);
       bin_mask &= ~((2u << BIN_G32) - 1u);
     }
