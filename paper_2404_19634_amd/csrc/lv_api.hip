@@ -1475,7 +1475,7 @@ lv_status modularity(const lv_graph* g, const int32_t* C, double* q_host, void* 
   L.w = g->w;
   LV_HIP(hipMemsetAsync(ws.ctr, 0, sizeof(int64_t) * CTR_COUNT, st));
   LV_HIP(hipMemsetAsync(ws.i64tmp, 0, sizeof(int64_t) * (static_cast<size_t>(g->n) + 1), st));
-  // K_i and the intra-community arc weight (ctr[AUX0]), then Σ_c and Σ_c^2
+  // K_i and the intra-community arc weight (ST_INTRA), then Σ_c and Σ_c^2
   launch_row_sums(L, C, ws.lK, nullptr, nullptr, nullptr, ws, st);
   launch_accumulate(C, g->n, nullptr, ws.lK, nullptr, ws.i64tmp, st);
   LV_HIP(hipMemsetAsync(ws.ctr + CTR_AUX1, 0, sizeof(int64_t), st));

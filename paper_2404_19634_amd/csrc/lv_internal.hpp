@@ -52,7 +52,9 @@ enum Ctr {
   CTR_T_CALL = 1,                // device clock (wall_clock64): the call's first kernel began,
   CTR_T_MOVE = 2,                // the pass's local-moving began
   CTR_TOTAL = 1 * kCtrLine,      // generic total (scans, counts)
-  CTR_AUX0 = 2 * kCtrLine,
+  CTR_EXPAND = 2 * kCtrLine,     // rows listed by the expansion of an iteration (k_expand_*).  The
+                                 // expansion's alone: zero at the call's start, left zero by its last
+                                 // kernel, so that its first one can append without a clear
   CTR_AUX1 = 3 * kCtrLine,
   CTR_AUX2 = 4 * kCtrLine,
   CTR_AUX3 = 5 * kCtrLine,

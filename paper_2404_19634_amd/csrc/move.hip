@@ -1880,7 +1880,7 @@ struct Expand {
   uint32_t* moved;
   uint32_t* next;
   uint8_t* flags;     // one byte per vertex, all zero between iterations
-  int32_t* longlist;  // ctr[CTR_AUX0] rows (that counter is the expansion's alone)
+  int32_t* longlist;  // ctr[CTR_EXPAND] rows (that counter is the expansion's alone)
   int64_t* ctr;
   const int64_t* sc;
 };
@@ -1903,7 +1903,7 @@ __device__ __forceinline__ void pull_words(const Expand& X) {
     const int64_t s = j < X.n ? X.row_start[j] : 0;
     if (len > kPullGroupMax) {
       const int64_t pos = static_cast<int64_t>(
-          atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_AUX0]), 1ull));
+          atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_EXPAND]), 1ull));
       X.longlist[pos] = static_cast<int32_t>(j);
       len = 0;
     }
@@ -1974,7 +1974,7 @@ __device__ __forceinline__ void push_words(const Expand& X) {
       s = X.row_start[i];
       if (len > kPushShortMax) {
         const int64_t pos =
-            static_cast<int64_t>(atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_AUX0]), 1ull));
+            static_cast<int64_t>(atomicAdd(reinterpret_cast<unsigned long long*>(&X.ctr[CTR_EXPAND]), 1ull));
         X.longlist[pos] = i;
         len = 0;
       }
@@ -2003,7 +2003,7 @@ __global__ void __launch_bounds__(kBlock) k_expand_words(Expand X, int64_t* __re
 }
 
 __global__ void __launch_bounds__(kBlock) k_expand_long(Expand X) {
-  const int64_t count = X.ctr[CTR_AUX0];
+  const int64_t count = X.ctr[CTR_EXPAND];
   if (blockIdx.x >= count) return;
   const bool push = expand_by_push(X.sc);
   for (int64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
@@ -2038,7 +2038,7 @@ __global__ void __launch_bounds__(kBlock) k_expand_long(Expand X) {
 // flags, movers and the list's count are cleared.
 __global__ void __launch_bounds__(kBlock) k_expand_end(Expand X, int64_t words) {
   const bool push = expand_by_push(X.sc);
-  if (blockIdx.x == 0 && threadIdx.x == 0) X.ctr[CTR_AUX0] = 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) X.ctr[CTR_EXPAND] = 0;
   for (int64_t w = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; w < words;
        w += static_cast<int64_t>(gridDim.x) * blockDim.x) {
     X.moved[w] = 0;
