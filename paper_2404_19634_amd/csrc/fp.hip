@@ -793,14 +793,12 @@ __global__ void __launch_bounds__(HUB ? kFWide : kBlock) k_f_scan_group(FMove M)
   }
 }
 
-// Frontier -> three bins (one thread per bitmask word), with the sub-round
-// filters of the integer path (hash round, degree class); the last round
-// clears the words it reads.  Workgroup counts per bin, one reservation.
+// Frontier -> three bins (one thread per bitmask word) of an iteration that
+// is one sub-round; the words read are cleared.  Workgroup counts per bin, one
+// reservation.
 __global__ void __launch_bounds__(kBlock) k_f_bin(uint32_t* __restrict__ cur, uint32_t* __restrict__ ever,
-                                                const int32_t* __restrict__ row_len, int32_t n, uint32_t round,
-                                                uint32_t shift, int32_t id_lo, int32_t id_hi, int32_t deg_lo,
-                                                int32_t deg_hi, int32_t clear,
-                                                int32_t* l0, int32_t* l1, int32_t* l2, int64_t* __restrict__ ctr) {
+                                                const int32_t* __restrict__ row_len, int32_t n, int32_t* l0,
+                                                int32_t* l1, int32_t* l2, int64_t* __restrict__ ctr) {
   __shared__ int32_t s_cnt[FB_N];
   __shared__ int64_t s_base[FB_N];
   int32_t* lists[FB_N] = {l0, l1, l2};
@@ -814,31 +812,7 @@ __global__ void __launch_bounds__(kBlock) k_f_bin(uint32_t* __restrict__ cur, ui
     uint32_t bits = 0;
     if (k < words) {
       bits = cur[k];
-      if (clear && bits) cur[k] = 0;
-      if (shift < 32 && bits) {
-        uint32_t keep = 0;
-        for (uint32_t r = bits; r; r &= r - 1) {
-          const uint32_t i = static_cast<uint32_t>(k * 32 + (__ffs(r) - 1));
-          if (((i * 0x9E3779B1u) >> shift) == round) keep |= 1u << (__ffs(r) - 1);
-        }
-        bits = keep;
-      }
-      if (bits && (id_lo > k * 32 || id_hi < (k + 1) * 32)) {
-        uint32_t keep = 0;
-        for (uint32_t r = bits; r; r &= r - 1) {
-          const int64_t i = k * 32 + (__ffs(r) - 1);
-          if (i >= id_lo && i < id_hi) keep |= 1u << (__ffs(r) - 1);
-        }
-        bits = keep;
-      }
-      if (bits && (deg_lo > 0 || deg_hi < INT_MAX)) {
-        uint32_t keep = 0;
-        for (uint32_t r = bits; r; r &= r - 1) {
-          const int32_t dg = row_len[k * 32 + (__ffs(r) - 1)];
-          if (dg >= deg_lo && dg <= deg_hi) keep |= 1u << (__ffs(r) - 1);
-        }
-        bits = keep;
-      }
+      if (bits) cur[k] = 0;
       if (ever && bits) {
         const uint32_t old = ever[k];
         affected += __popc(bits & ~old);
@@ -1430,10 +1404,9 @@ lv_status run_f(bool df, const lv_graph_f* g, const lv_edges_f* del, const lv_ed
       if (plan.size() > 1) {
         if ((s = planned_rounds_f(M, w, cur, pass == 0 ? w.ever : nullptr, plan, tu, S, st))) return s;
       } else {
-        const SubRound& r = plan[0];
         hipLaunchKernelGGL(k_f_bin, dim3(blocks(w.words, 4096)), dim3(kBlock), 0, st, cur,
-                           pass == 0 ? w.ever : nullptr, L.row_len, L.n, r.hash_round, r.hash_shift, r.id_lo, r.id_hi,
-                           r.deg_lo, r.deg_hi, 1, w.list[FB_WAVE], w.list[FB_BLOCK], w.list[FB_HUB], w.ctr);
+                           pass == 0 ? w.ever : nullptr, L.row_len, L.n, w.list[FB_WAVE], w.list[FB_BLOCK],
+                           w.list[FB_HUB], w.ctr);
         const int64_t e = std::max<int64_t>(64, est);
         launch_scans_f(M, 7u, e, e, e, st);
       }
