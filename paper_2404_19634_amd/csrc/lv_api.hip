@@ -137,7 +137,7 @@ namespace {
 
 // Timing events, one set per host thread.
 struct Events {
-  hipEvent_t e[8] = {};
+  hipEvent_t e[4] = {};  // aggregation begin, end; output begin, end
   bool made = false;
   ~Events() {
     if (made)
@@ -778,7 +778,7 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     const int32_t nc = nc32;
     S.communities[pass] = nc;
     if (static_cast<double>(nc) / static_cast<double>(L.n) > p->aggregation_tolerance) break;
-    LV_HIP(record(ev, 4, st));
+    LV_HIP(record(ev, 0, st));
     launch_relabel(Cl, L.n, ws.newid, st);
     if (pass > 0) launch_lookup(state->C, N, Cl, st);
     LevelGraph out = ws.lg[pass & 1];
@@ -787,11 +787,11 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     LV_HIP(hipMemsetAsync(cur, 0, sizeof(uint32_t) * ws.words, st));
     launch_set_all_bits(cur, nc, st);
     launch_list_invalid(cur_fl, st);
-    LV_HIP(record(ev, 5, st));
+    LV_HIP(record(ev, 1, st));
     LV_HIP(hipMemcpyAsync(&host[CTR_COUNT], out.row_start + nc, sizeof(int64_t), hipMemcpyDeviceToHost, st));
     if ((s = read_counters(host, ws, CTR_STATS0, st))) return s;
     if (host[CTR_ERR]) return device_error(host[CTR_ERR], "aggregation");
-    ms_agg += ms_between(ev, 4, 5);
+    ms_agg += ms_between(ev, 0, 1);
     arcs_agg += host[CTR_COUNT];
     L = out;
     Cl = ws.lC;
@@ -802,14 +802,14 @@ lv_status run_louvain(Approach ap, const lv_graph* g, const lv_edges* del, const
     aggregated = true;
   }
   if (aggregated) {
-    LV_HIP(record(ev, 6, st));
+    LV_HIP(record(ev, 2, st));
     launch_lookup(state->C, N, Cl, st);
     launch_sigma_from_members(state->C, state->K, N, state->Sigma, st);
     if (state->size) launch_community_sizes(state->C, N, state->size, st);
     LV_CHECK_LAUNCH();
-    LV_HIP(record(ev, 7, st));
+    LV_HIP(record(ev, 3, st));
     LV_HIP(hipStreamSynchronize(st));
-    S.ms_other = ms_between(ev, 6, 7);
+    S.ms_other = ms_between(ev, 2, 3);
   }
   timer_collect(S.timed_launches, S.timed_ms);
   S.ms_mark = ms_mark;
