@@ -121,17 +121,15 @@ __global__ void k_relayout_copy(const int64_t* __restrict__ s_start, const int32
 //  - longer rows are listed in chunks of kChunk arcs, one wavefront per
 //    chunk, whose partial sums are added atomically (K and Sigma of such a
 //    row are zeroed by the first kernel).
-// With C the cost is the gather of C[j] per arc.  On graphs whose C exceeds
-// an XCD's 4 MB L2 each gather moves a 128-byte line from beyond it, so a
-// one-byte hash tag per vertex (a quarter of C) is gathered first and C
-// only where the tags agree.
+// With C the cost is the gather of C[j] per arc, a line of L1 each.  (A one-byte
+// hash tag of C gathered first, and C where the tags agree, fits the caches
+// four times better but costs a second, dependent gather per arc inside a
+// community.  Power-law graph of 4M vertices, with tags and without: random
+// labels 1494 and 1708 us, 20% of the weight inside communities 1740 and 1707,
+// 75%, as a clustering has it, 2469 and 1705.)
 // The lists are kept per region (row task mod kRegions), each region with
 // its own counters, so a workgroup reserves its entries with one atomic per
 // class on a counter shared with few others.
-// Vertices above which the tags are made and used: C of 4 MB.  Modularity of
-// an R-MAT graph of 4.2M vertices and 128M arcs: 1414 us without them, 1242
-// with them, 1060 with the packed short rows and the sums of hist.hip.
-constexpr int32_t kTagMinVertices = 1 << 20;
 constexpr int kLaneMax = 16;
 constexpr int kGroupMax = 64;
 constexpr int kMidMax = 4096;
@@ -152,41 +150,22 @@ struct RowSumOut {
   int32_t* mid;    // wavefront rows, likewise
   int64_t cap;     // list entries per region
   int64_t* cnt;    // region r's counts: cnt[(2r) * kCtrLine] (group), cnt[(2r + 1) * kCtrLine] (wavefront)
-  const uint8_t* tag;  // label_tag of every vertex's community, or null
 };
 
-__device__ __forceinline__ uint8_t label_tag(int32_t c) {
-  return static_cast<uint8_t>((static_cast<uint32_t>(c) * 0x9E3779B1u) >> 24);
-}
-
-__global__ void k_label_tags(const int32_t* __restrict__ C, int32_t n, uint8_t* __restrict__ tag) {
-  for (int64_t i = (blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x) * 4; i < n;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x * 4) {
-    uint32_t t = 0;
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      if (i + q < n) t |= static_cast<uint32_t>(label_tag(C[i + q])) << (8 * q);
-    *reinterpret_cast<uint32_t*>(tag + i) = t;  // (the tag array is padded to whole words)
-  }
-}
-
-// Weight of the arcs (j, x) into community ci; j < 0: none.  The gathers of
-// all N arcs are issued together.
+// Weight of the arcs (j, x) into community ci; j < 0: none, and x is 0.  The
+// gathers of all N arcs are issued together, behind all of their loads (one
+// by one behind each: an R-MAT graph of 4.2M vertices 1226 us, together 1118).
 template <int N>
-__device__ __forceinline__ int64_t inside(const int32_t* __restrict__ C, const uint8_t* __restrict__ tag, int32_t ci,
-                                          const int32_t (&j)[N], const int32_t (&x)[N]) {
-  int32_t c[N];
-  if (tag) {
-    const uint8_t own = label_tag(ci);
-    uint8_t t[N];
+__device__ __forceinline__ int64_t inside(const int32_t* __restrict__ C, int32_t ci, const int32_t (&j)[N],
+                                          const int32_t (&x)[N]) {
+  int32_t c[N], at[N];
 #pragma unroll
-    for (int q = 0; q < N; ++q) t[q] = j[q] >= 0 ? tag[j[q]] : static_cast<uint8_t>(~own);
-#pragma unroll
-    for (int q = 0; q < N; ++q) c[q] = t[q] == own ? C[j[q]] : ~ci;
-  } else {
-#pragma unroll
-    for (int q = 0; q < N; ++q) c[q] = j[q] >= 0 ? C[j[q]] : ~ci;
+  for (int q = 0; q < N; ++q) {
+    at[q] = j[q];
+    asm("" : "+v"(at[q]));  // (else the address is formed in the branch of j's own load, which then waits for it)
   }
+#pragma unroll
+  for (int q = 0; q < N; ++q) c[q] = C[max(at[q], 0)];  // (no arc: x is 0)
   int64_t sum = 0;
 #pragma unroll
   for (int q = 0; q < N; ++q) sum += c[q] == ci ? x[q] : 0;
@@ -197,8 +176,8 @@ __device__ __forceinline__ int64_t inside(const int32_t* __restrict__ C, const u
 // Sum of arcs [a, b) of the row starting at s, over the wavefront, 256 arcs
 // per step; with C, adds the weight of arcs into community ci to *intra.
 __device__ __forceinline__ int64_t wave_row_sum(const int32_t* __restrict__ col, const int32_t* __restrict__ wt,
-                                                const int32_t* __restrict__ C, const uint8_t* __restrict__ tag,
-                                                int64_t s, int32_t a, int32_t b, int32_t ci, int64_t* intra) {
+                                                const int32_t* __restrict__ C, int64_t s, int32_t a, int32_t b,
+                                                int32_t ci, int64_t* intra) {
   const int lane = lane_id();
   int64_t acc = 0;
   for (int32_t k0 = a + lane; k0 < b; k0 += kWave * kRowUnroll) {
@@ -211,7 +190,7 @@ __device__ __forceinline__ int64_t wave_row_sum(const int32_t* __restrict__ col,
     }
 #pragma unroll
     for (int q = 0; q < kRowUnroll; ++q) acc += x[q];
-    if (C) *intra += inside(C, tag, ci, j, x);
+    if (C) *intra += inside(C, ci, j, x);
   }
   return wave_sum_i64(acc);
 }
@@ -299,7 +278,7 @@ __global__ void __launch_bounds__(kBlock) k_rows_flat(const int64_t* __restrict_
       int64_t sum = 0;
 #pragma unroll
       for (int q = 0; q < kLaneMax / 4; ++q) sum += x[q];
-      if (C) intra += inside(C, o.tag, rc, j, x);
+      if (C) intra += inside(C, rc, j, x);
       sum += __shfl_xor(sum, 1);
       sum += __shfl_xor(sum, 2);
       if (on && lane % 4 == 0) {
@@ -373,7 +352,7 @@ __global__ void __launch_bounds__(kBlock) k_rows_grp(const int64_t* __restrict__
     int64_t acc = 0;
 #pragma unroll
     for (int q = 0; q < kGroupMax / 16; ++q) acc += x[q];
-    if (C) intra += inside(C, o.tag, ci, j, x);
+    if (C) intra += inside(C, ci, j, x);
     for (int m = 8; m > 0; m >>= 1) acc += __shfl_xor(acc, m, 16);
     if (sub == 0) {
       o.K[i] = acc;
@@ -406,7 +385,7 @@ __global__ void __launch_bounds__(kBlock) k_rows_mid(const int64_t* __restrict__
     const int64_t ns = ni >= 0 ? row_start[ni] : 0;
     const int32_t nlen = ni >= 0 ? row_len[ni] : 0;
     const int32_t nci = (C && ni >= 0) ? C[ni] : 0;
-    const int64_t sum = wave_row_sum(col, wt, C, o.tag, s, 0, len, ci, &intra);
+    const int64_t sum = wave_row_sum(col, wt, C, s, 0, len, ci, &intra);
     if (lane_id() == 0) {
       o.K[i] = sum;
       if (o.Sigma) o.Sigma[i] = sum;
@@ -435,7 +414,7 @@ __global__ void __launch_bounds__(kBlock) k_rows_chunks(const int64_t* __restric
     const int32_t a = o.loff[idx];
     const int32_t b = min(row_len[i], a + kChunk);
     const int32_t ci = C ? C[i] : 0;
-    const int64_t sum = wave_row_sum(col, wt, C, o.tag, row_start[i], a, b, ci, &intra);
+    const int64_t sum = wave_row_sum(col, wt, C, row_start[i], a, b, ci, &intra);
     if (lane_id() == 0 && sum) {
       atomic_add_i64(&o.K[i], sum);
       if (o.Sigma) atomic_add_i64(&o.Sigma[i], sum);
@@ -533,13 +512,7 @@ void launch_row_sums(const LevelGraph& g, const int32_t* C_mod, int64_t* K, int6
   // tasks of kBlock rows
   const int64_t tasks = (static_cast<int64_t>(g.n) + kBlock - 1) / kBlock;
   const int64_t cap = (tasks + kRegions - 1) / kRegions * kBlock;
-  RowSumOut o{K, Sigma, Cinit, size, ws.u_ins_b, ws.u_emit_b, ws.ctr, ws.bins[0], ws.bins[1], cap, cnt,
-              nullptr};
-  if (C_mod && g.n > kTagMinVertices) {
-    hipLaunchKernelGGL(k_label_tags, dim3(grid_for((static_cast<int64_t>(g.n) + 3) / 4, kBlock, 8192)), dim3(kBlock), 0,
-                       st, C_mod, g.n, ws.push_flags);
-    o.tag = ws.push_flags;
-  }
+  RowSumOut o{K, Sigma, Cinit, size, ws.u_ins_b, ws.u_emit_b, ws.ctr, ws.bins[0], ws.bins[1], cap, cnt};
   hipLaunchKernelGGL(k_rows_flat, dim3(static_cast<uint32_t>(std::min<int64_t>(tasks, 8192))), dim3(kBlock), 0, st,
                      g.row_start, g.row_len, g.col, g.w, g.n, C_mod, o);
   // (grids of many waves, so the memory latencies of the rows overlap; the
