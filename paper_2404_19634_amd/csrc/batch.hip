@@ -233,13 +233,18 @@ __global__ void k_place(Upd<W> U, BatchScratch b) {
 
 // One wavefront per chunk: every arc of the chunk is tested against the
 // row's partners; hits are looked up in the pair table and their positions
-// recorded per (pair, direction).  Up to kDirect partners are compared one by
-// one from a register; more go to a filter in LDS, except where the chunk has
-// at most an arc per lane: every arc is looked up.  (Those lookups, a gather
-// per arc, bound the scan while they served all short rows: 62 us for the
-// 100,000 rows of a 50,000-update batch, most of one or two partners; compared:
-// 46 us, and 23 -> 18 us for 16,000 updates of a 2^20-vertex R-MAT graph.)
-constexpr int kDirect = 16;
+// recorded per (pair, direction).  A few partners are compared one by one from
+// a register: up to kDirectShort where the chunk has at most an arc per lane
+// (more: every arc is looked up), up to kDirect in longer chunks (more: a
+// filter in LDS).  (Lookups, a gather per arc, bound the scan while they served
+// all short rows: 62 us for the 100,000 rows of a 50,000-update batch, most of
+// one or two partners; compared: 46 us, and 23 -> 18 us for 16,000 updates of
+// a 2^20-vertex R-MAT graph.  In long rows the filter is the faster from five
+// partners on: an edit of 1024 rows of 20,000 arcs takes, compared and
+// filtered, 97 and 98 us with 4 partners a row, 103 and 98 with 6, 106 and 95
+// with 8, 128 and 99 with 16.)
+constexpr int kDirect = 4;
+constexpr int kDirectShort = 16;
 __global__ void __launch_bounds__(kBlock) k_scan(const int64_t* __restrict__ row_start,
                                                  const int32_t* __restrict__ col, BatchScratch b,
                                                  const int64_t* __restrict__ ctr) {
@@ -257,7 +262,7 @@ __global__ void __launch_bounds__(kBlock) k_scan(const int64_t* __restrict__ row
     if (ch + nwaves < chunks) next = b.chunk[ch + nwaves];
     const int32_t a = c.a, cnt = c.cnt, pbase = c.pbase, off = c.off, end = c.end;
     const int64_t s = c.s;
-    if (cnt <= kDirect) {
+    if (cnt <= (end - off <= kWave ? kDirectShort : kDirect)) {
       const int32_t mine = lane < cnt ? b.part[pbase + lane] : -1;
       for (int32_t k0 = off + lane; k0 - lane < end; k0 += 4 * kWave) {
         int32_t cc[4];
