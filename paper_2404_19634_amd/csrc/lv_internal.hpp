@@ -737,8 +737,9 @@ void timer_weight(const TimerPair& p, int launches);
 TimerPair timer_pair(int kernel);
 void timer_collect(int32_t* launches, double* ms);  // adds per kernel, resets
 
-// One sub-round: binning, hub table clear, the fused scan over the bins in
-// `bin_mask` (and hub inserts), hub decisions.  Four launches.
+// One sub-round that picks its own vertices: binning, then launch_scan (with
+// hub rows the table clear, the scan over the bins in `bin_mask` in one launch
+// or several, the hub decisions, their final and the expansion).
 uint32_t bins_for_degrees(int32_t lo, int32_t hi, int32_t wave_max);
 void launch_round(const MoveArgs& a, Workspace& ws, const lv_tuning& tu, const SubRound& r, uint32_t bin_mask,
                   bool expand, hipStream_t st);

@@ -30,8 +30,19 @@ __device__ __forceinline__ bool update_ok(int32_t a, int32_t b, int32_t n) {
 }
 
 // Updates per thread: one up to kUwFew updates, where more workgroups shorten
-// the chain (16,000 updates: 16 us with four, 12 with one); beyond, fewer
-// workgroups flush fewer tables into the same totals (50,000: 23, 42).
+// the chain; beyond, four, where fewer workgroups flush fewer tables into the
+// same totals.  From the call's begin to its first binning on 2,000,000
+// vertices, us with one / with four:
+//   updates   8 communities  64         1000       30,000     2,000,000
+//   2000      11 / 18        11 / 17    11 / 17    11 / 28    11 / 28
+//   16,000    16 / 20        21 / 20    14 / 19    12 / 28    12 / 33
+//   24,000    20 / 22        27 / 21    17 / 18    14 / 29    14 / 30
+//   32,000    24 / 21        33 / 22    20 / 21    16 / 29    15 / 33
+//   50,000    33 / 23        48 / 29    26 / 22    21 / 30    20 / 31
+//   100,000   55 / 37        90 / 43    47 / 37    35 / 41    32 / 42
+// The sides cross between 16,000 updates (64 communities) and beyond 100,000
+// (30,000 and more).  The rule knows the updates only: at its line one per
+// thread loses at most 6 us, four would lose up to 16.
 constexpr int kUwItemsMany = 4;
 constexpr int64_t kUwFew = 24576;
 constexpr int kUwSlots = 2048;                      // LDS table slots
