@@ -774,8 +774,8 @@ void launch_many_df(const int32_t* count, ManyItem* items, int32_t grid, const l
   // Up to two graphs per compute unit, a launch lasts as long as its largest
   // graph, which has the unit nearly to itself: 16 wavefronts work on it.
   // Burst of 256 graphs of 1000 to 50,000 vertices (1e-3 |E| batches), whole
-  // call: 1347 us with 256 threads, 774 with 1024 (the kernel 890 and 321;
-  // 290 with the rows prefetched).  With more graphs the units are full
+  // call: 1347 us with 256 threads, 778 with 1024 (the kernel 890 and 321;
+  // 282 with the rows prefetched).  With more graphs the units are full
   // either way: 512 graphs of up to 20,000 vertices 1331 and 1128 us, 1024 of
   // up to 4000 vertices take the same.
   if (wide)
